@@ -5,7 +5,8 @@
 // bf16: MFMA tiles staged through LDS (by LDS DMA for the main kernels):
 // 256 x 256 and 256 x 128 tiles of v_mfma_f32_32x32x16_bf16 for hundreds of
 // rows and more, streaming tiles of v_mfma_f32_16x16x32_bf16 for up to 128
-// rows.  fp32: a plain LDS-tiled FMA kernel (used by the fp32 model).
+// rows.  fp32: v_mfma_f32_16x16x4_f32 with operands loaded straight into
+// their lanes (used by the fp32 model).
 // Split-K writes fp32 partials [split][M][Nout] that a consumer sums in
 // split order, so results do not depend on scheduling.
 #include <cstdlib>
@@ -1256,55 +1257,123 @@ gemm_ring_kernel(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict
 }
 
 // ------------------------------------------------------------ fp32 GEMM
-// 64 x 64 block tile, 256 threads, 4 x 4 outputs per thread, K step 16.
-// Always writes to `partial` ([1][M][NB*N]); the reduce kernel applies the
-// epilogue.
+// v_mfma_f32_16x16x4_f32 (full fp32 products and sums) with both operands
+// loaded from memory straight into their lanes: lane l of a 16-row block
+// holds row l % 16 and, of every 16 values of K, the four 4 (l / 16) .. + 3,
+// fed to four MFMAs (the contraction visits K in that order; A and B alike).
+// The weight fragment is the first operand, so a lane accumulates four
+// consecutive output columns.  Work-group = 4 waves:
+//   KW = 4: one (16 TI) x (16 TJ) tile, the waves splitting K into quarters
+//     that are summed in wave order through LDS.  The fp32 model's
+//     projections (K 128-512, a few rows) are one memory round trip long and
+//     nothing else: a whole call of the tiny configuration (16 candidates, 64
+//     tokens) went from 24.8 to 5.2 ms against a 64 x 64 LDS-tiled FMA kernel
+//     (two barriers per 16 of K: 21 us at K 128, 77 us at K 512) and its
+//     reduce launch.
+//   KW = 1: a 2 x 2 grid of wave tiles, each the whole K, for grids that fill
+//     the chip with 64 x 64 tiles (the operands come from L1 / L2).
+// AL: operand rows are 16-byte aligned (float4 loads), else four scalar loads.
+template <int TI, int TJ, int KW, bool PAIRED, bool AL>
 __global__ void __launch_bounds__(256)
-gemm_f32_kernel(const float* __restrict__ A, int lda, const float* __restrict__ B, int ldb,
-                int64_t pair_off, int paired, int M, int N, int K, float* __restrict__ partial) {
-  __shared__ float As[16][64 + 1];
-  __shared__ float Bs[16][64 + 1];
-  const int tid = threadIdx.x;
-  const int tx = tid % 16, ty = tid / 16;
-  const int m0 = blockIdx.y * 64;
-  const int nb = paired ? 2 : 1;
-  const int ncols = nb * N;
-  const int n0 = blockIdx.x * 64;  // over the concatenated [gate | up] columns
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    for (int c = tid; c < 64 * 16; c += 256) {
-      int r = c / 16, kk = c % 16;
-      int m = m0 + r, n = n0 + r;
-      As[kk][r] = (m < M) ? A[(int64_t)m * lda + k0 + kk] : 0.f;
-      float bv = 0.f;
-      if (n < ncols) {
-        int blk = n / N, nn = n % N;
-        bv = B[blk * pair_off + (int64_t)nn * ldb + k0 + kk];
-      }
-      Bs[kk][r] = bv;
+gemm_f32_kernel(const float* __restrict__ A, int lda, const float* __restrict__ B, int ldb, int64_t pair_off, int M,
+                int N, int K, EpiArgs epi, float* __restrict__ partial) {
+  constexpr int NB = PAIRED ? 2 : 1;
+  constexpr int UN = KW == 4 ? 4 : 2;  // 16-wide K chunks loaded together
+  static_assert(KW == 1 || KW == 4, "K split over the waves");
+  __shared__ __attribute__((aligned(16))) float red[KW == 4 ? 3 * NB * TI * TJ * 256 : 4];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int fr = lane & 15, fg = lane >> 4;
+  constexpr int BM = KW == 4 ? 16 * TI : 32 * TI, BN = KW == 4 ? 16 * TJ : 32 * TJ;
+  const int m0 = blockIdx.y * BM + (KW == 4 ? 0 : (wave >> 1) * 16 * TI);
+  const int n0 = blockIdx.x * BN + (KW == 4 ? 0 : (wave & 1) * 16 * TJ);
+  const int kw = K / KW, kb = KW == 4 ? wave * kw : 0;
+
+  const float *ap[TI], *bp[NB][TJ];
+#pragma unroll
+  for (int i = 0; i < TI; ++i) ap[i] = A + (int64_t)min(m0 + 16 * i + fr, M - 1) * lda + kb + 4 * fg;
+#pragma unroll
+  for (int b = 0; b < NB; ++b)
+#pragma unroll
+    for (int j = 0; j < TJ; ++j)
+      bp[b][j] = B + b * pair_off + (int64_t)min(n0 + 16 * j + fr, N - 1) * ldb + kb + 4 * fg;
+  auto load = [](const float* p) {
+    if constexpr (AL) return *reinterpret_cast<const f32x4*>(p);
+    else return f32x4{p[0], p[1], p[2], p[3]};
+  };
+  f32x4 acc[NB][TI][TJ];
+#pragma unroll
+  for (int b = 0; b < NB; ++b)
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+      for (int j = 0; j < TJ; ++j) acc[b][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto chunks = [&](auto un, int k) {
+    constexpr int U = decltype(un)::value;
+    f32x4 a[U][TI], w[U][NB][TJ];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int j = 0; j < TJ; ++j) w[u][b][j] = load(bp[b][j] + k + 16 * u);
+#pragma unroll
+      for (int i = 0; i < TI; ++i) a[u][i] = load(ap[i] + k + 16 * u);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+          for (int i = 0; i < TI; ++i)
+#pragma unroll
+            for (int j = 0; j < TJ; ++j)
+              acc[b][i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[u][b][j][e], a[u][i][e], acc[b][i][j], 0, 0, 0);
+  };
+  int k = 0;
+  for (; k + 16 * UN <= kw; k += 16 * UN) chunks(std::integral_constant<int, UN>{}, k);
+  for (; k < kw; k += 16) chunks(std::integral_constant<int, 1>{}, k);
+
+  if constexpr (KW == 4) {
+    f32x4* r4 = reinterpret_cast<f32x4*>(red);
+    if (wave > 0) {
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
+          for (int j = 0; j < TJ; ++j)
+            r4[(((wave - 1) * NB + b) * TI * TJ + i * TJ + j) * 64 + lane] = acc[b][i][j];
     }
     __syncthreads();
+    if (wave > 0) return;
 #pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      float a[4], b[4];
+    for (int w = 0; w < 3; ++w)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[kk][ty * 4 + i];
+      for (int b = 0; b < NB; ++b)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = Bs[kk][tx * 4 + j];
+        for (int i = 0; i < TI; ++i)
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
+          for (int j = 0; j < TJ; ++j) acc[b][i][j] += r4[((w * NB + b) * TI * TJ + i * TJ + j) * 64 + lane];
   }
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < TI; ++i) {
+    const int m = m0 + 16 * i + fr;
+    if (m >= M) continue;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      int m = m0 + ty * 4 + i, n = n0 + tx * 4 + j;
-      if (m < M && n < ncols) partial[(int64_t)m * ncols + n] = acc[i][j];
-    }
+    for (int j = 0; j < TJ; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int n = n0 + 16 * j + 4 * fg + e;
+        if (n >= N) break;
+        const float v = PAIRED ? silu(acc[0][i][j][e]) * acc[NB - 1][i][j][e] : acc[0][i][j][e];
+        if (partial) partial[(int64_t)m * N + n] = v;
+        else if (PAIRED) store_out(epi, m, n, v);
+        else epi_one(epi, m, n, v);
+      }
+  }
 }
 
 // Sum split-K partials in split order, then apply the epilogue.
@@ -1461,17 +1530,35 @@ int gemm(const GemmArgs& g, float* partial, size_t partial_cap, hipStream_t s) {
   EpiArgs e{g.epi, g.out, g.ldo, g.out_bf16};
   if (g.M == 0 || g.N == 0) return 1;
   if (g.dtype == SR_F32) {
-    const int ncols = (g.paired ? 2 : 1) * g.N;
-    SR_REQUIRE((size_t)g.M * ncols <= partial_cap, 5, "GEMM partial buffer too small");
-    dim3 grid((ncols + 63) / 64, (g.M + 63) / 64);
-    SR_LAUNCH(gemm_f32_kernel, grid, dim3(256), 0, s, (const float*)g.A, g.lda,
-                       (const float*)g.B, g.ldb, g.pair_off, (int)g.paired, g.M, g.N, g.K, partial);
-    SR_CHECK_LAUNCH();
-    if (g.epi == EPI_PARTIAL) return 1;
-    int64_t total = (int64_t)g.M * g.N;
-    int blocks = (int)std::min<int64_t>((total + 255) / 256, 4096);
-    SR_LAUNCH(gemm_reduce_kernel, dim3(blocks), dim3(256), 0, s, partial, 1, g.M, g.N,
-                       (int)g.paired, e);
+    float* part = g.epi == EPI_PARTIAL ? partial : nullptr;
+    if (part) SR_REQUIRE((size_t)g.M * g.N <= partial_cap, 5, "GEMM partial buffer too small");
+    const bool al = ((reinterpret_cast<uintptr_t>(g.A) | reinterpret_cast<uintptr_t>(g.B)) & 15) == 0 &&
+                    g.lda % 4 == 0 && g.ldb % 4 == 0 && g.pair_off % 4 == 0;
+    // 64 x 64 tiles once they alone give every CU a work-group; below that
+    // 16 x 16 tiles with K split over the waves (3000 rows of the tiny
+    // shape's QKV: 282 tiles of 64 x 64)
+    const bool wide = (int64_t)((g.M + 63) / 64) * ((g.N + 63) / 64) >= 256;
+    const int bt = wide ? 64 : 16;
+    const int64_t gy = (g.M + bt - 1) / bt;
+    SR_REQUIRE(gy <= 65535, SR_ERR_UNSUPPORTED, "fp32 GEMM: too many rows");
+    const dim3 grid((g.N + bt - 1) / bt, (unsigned)gy);
+#define SR_GEMM32(TI, TJ, KW, P, AL)                                                                             \
+  SR_LAUNCH((gemm_f32_kernel<TI, TJ, KW, P, AL>), grid, dim3(256), 0, s, (const float*)g.A, g.lda,            \
+            (const float*)g.B, g.ldb, g.pair_off, g.M, g.N, g.K, e, part)
+#define SR_GEMM32_AL(TI, TJ, KW, P)         \
+  do {                                   \
+    if (al) SR_GEMM32(TI, TJ, KW, P, true); \
+    else SR_GEMM32(TI, TJ, KW, P, false);   \
+  } while (0)
+    if (wide) {
+      if (g.paired) SR_GEMM32_AL(2, 2, 1, true);
+      else SR_GEMM32_AL(2, 2, 1, false);
+    } else {
+      if (g.paired) SR_GEMM32_AL(1, 1, 4, true);
+      else SR_GEMM32_AL(1, 1, 4, false);
+    }
+#undef SR_GEMM32_AL
+#undef SR_GEMM32
     SR_CHECK_LAUNCH();
     return 1;
   }

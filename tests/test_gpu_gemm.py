@@ -96,3 +96,30 @@ def test_projection_paired_8b(M):
     g, u = x64 @ w64[0].T, x64 @ w64[1].T
     ref = g / (1 + np.exp(-g)) * u
     assert np.abs(got - ref).max() <= 1e-2 * np.abs(ref).max(), np.abs(got - ref).max()
+
+
+@pytest.mark.parametrize("mode", [0, 1, 2])
+@pytest.mark.parametrize("M,N,K", [(5, 33, 64), (17, 100, 192), (1090, 1000, 64)])
+def test_projection_f32_unaligned(M, N, K, mode):
+    """fp32 operands that are only 4-byte aligned (scalar loads), on the
+    split-K and the whole-K tiles.  Bound: K + 2 roundings of sums of |x w|,
+    2^-24 each, on max-abs products well below 1."""
+    torch, sr = need_gpu()
+    say(f"projection f32 unaligned mode={mode} M={M} N={N} K={K}")
+    rng = np.random.default_rng(M + N + K + mode)
+    x = rng.normal(0, 1, size=(M, K)).astype(np.float32)
+    w = rng.normal(0, 0.05, size=((2, N, K) if mode == 2 else (N, K))).astype(np.float32)
+    xt = torch.from_numpy(np.concatenate([np.zeros(1, np.float32), x.ravel()])).cuda()[1:].view(M, K)
+    wt = torch.from_numpy(np.concatenate([np.zeros(1, np.float32), w.ravel()])).cuda()[1:].view(w.shape)
+    init = rng.normal(size=(M, N)).astype(np.float32)
+    out = torch.from_numpy(init.copy()).cuda()
+    sr.projection(xt, wt, mode, out)
+    torch.cuda.synchronize()
+    x64, w64 = x.astype(np.float64), w.astype(np.float64)
+    if mode == 2:
+        g, u = x64 @ w64[0].T, x64 @ w64[1].T
+        ref = g / (1 + np.exp(-g)) * u
+    else:
+        ref = x64 @ w64.T + (init if mode == 1 else 0)
+    bound = (K + 2) * 2.0 ** -24 * max(1.0, float((np.abs(x64) @ np.abs(w64.reshape(-1, K)).T).max())) ** 2
+    assert np.abs(out.cpu().numpy() - ref).max() <= bound
