@@ -110,3 +110,30 @@ def test_compact_bit_exact(elem_bytes, hd):
         Dd = dst[blk * db: blk * db + b * hkv * cap_dst * hd].reshape(b, hkv, cap_dst, hd)
         assert np.array_equal(Dd[: len(kept), :, :length], S[kept, :, :length])
         assert not Dd[len(kept):].any() and not Dd[:, :, length:].any()
+
+
+@pytest.mark.parametrize("b,keep_frac,length,hkv,hd", [(1, 1.0, 1, 1, 64), (300, 0.0, 5, 2, 64), (257, 1.0, 65, 3, 128),
+                                                       (4096, 0.02, 3, 1, 64), (9, 0.5, 0, 2, 64),
+                                                       (40, 0.6, 130, 8, 128)])
+def test_compact_edges(b, keep_frac, length, hkv, hd):
+    """Compaction at the edges of its packing and chunks: one row, no row and
+    every row kept, the most rows, no tokens, runs of just over one and two
+    16 KB chunks."""
+    torch, sr = need_gpu()
+    say(f"compact b={b} keep={keep_frac} len={length} hkv={hkv} hd={hd}")
+    rng = np.random.default_rng(b + length)
+    nl, cap = 2, max(length, 1)
+    blk = b * hkv * cap * hd
+    src = torch.from_numpy(rng.integers(0, 2**15, size=(2 * nl, b, hkv, cap, hd)).astype(np.int16)).cuda()
+    dst = torch.zeros_like(src)
+    flags = (rng.random(b) < keep_frac).astype(np.int32)
+    src_row = torch.full((b,), -1, dtype=torch.int32, device="cuda")
+    cnt = torch.full((1,), -1, dtype=torch.int32, device="cuda")
+    sr.compact(src, blk, dst, blk, torch.from_numpy(flags).cuda(), nl, hkv, hd, 2, cap, cap, length, src_row, cnt)
+    torch.cuda.synchronize()
+    kept = np.flatnonzero(flags)
+    assert int(cnt.item()) == len(kept)
+    assert np.array_equal(src_row.cpu().numpy()[: len(kept)], kept) and bool((src_row[len(kept):] == -1).all())
+    ref = torch.zeros_like(src)
+    ref[:, : len(kept), :, :length] = src[:, torch.from_numpy(kept).cuda(), :, :length]
+    assert torch.equal(dst, ref)
