@@ -137,3 +137,34 @@ def test_compact_edges(b, keep_frac, length, hkv, hd):
     ref = torch.zeros_like(src)
     ref[:, : len(kept), :, :length] = src[:, torch.from_numpy(kept).cuda(), :, :length]
     assert torch.equal(dst, ref)
+
+
+@pytest.mark.parametrize("vocab", [24576, 24577, 24579, 32768, 50257, 131071, 262144])
+@pytest.mark.parametrize("temperature", [1.0, 0.3, 0.0])
+def test_sampler_segment_edges(vocab, temperature):
+    """Vocabularies around the change of segment length, odd ones (rows that
+    are not 16-byte aligned) and the largest; NaN, infinities, several
+    maxima, rows without a distribution and late steps."""
+    torch, sr = need_gpu()
+    say(f"sampler edges vocab={vocab} T={temperature}")
+    rng = np.random.default_rng(vocab + 1)
+    rows = 13
+    logits = (rng.standard_normal((rows, vocab)) * rng.uniform(0.5, 8.0, size=(rows, 1))).astype(np.float32)
+    logits[0, ::3] = np.nan
+    logits[1] = -np.inf
+    logits[2, 5:] = -np.inf
+    logits[3, vocab - 40:] = 9.0                    # many weights of exactly 2^32, at the row's end
+    logits[4] = np.nextafter(np.float32(1), np.float32(0))
+    logits[4, 7::11] = 1.0
+    logits[5] = -0.0
+    logits[5, vocab // 3] = 0.0
+    logits[6] = np.nan
+    logits[7, vocab - 1] = 60.0
+    logits[8] -= 3.0e38
+    cand = rng.permutation(4096)[:rows].astype(np.int32)
+    for step in (0, 517):
+        tok = torch.empty(rows, dtype=torch.int32, device="cuda")
+        sr.sample(torch.from_numpy(logits).cuda(), torch.from_numpy(cand).cuda(), step, temperature, 1 << 40 | 9, tok)
+        with np.errstate(all="ignore"):
+            ref = oracle_tokens(logits, cand, step, temperature, 1 << 40 | 9)
+        assert np.array_equal(tok.cpu().numpy(), ref), (step, np.flatnonzero(tok.cpu().numpy() != ref))
