@@ -12,16 +12,17 @@
 //                        one (row, KV head), its waves split the keys;
 //   decode_attn_kernel   (fp32 and head_dim 32): vector ALU, 16-byte loads,
 //                        DPP reductions;
-//   prefill_attn_mfma_kernel<.., true>: the prefix of 16 rows at once, for
-//                        the one-query-head-per-KV-head case at 128+ rows.
+//   prefix_attn_mfma_kernel: the prefix of 16 rows at once, for the
+//                        one-query-head-per-KV-head case at 128+ rows.
 // Online softmax in base 2; split partials are merged by log-sum-exp.
 //
 // Prefill (reward-model scoring, prompt): a work-group owns 8 / G blocks of
-// 16 queries of one row and one KV head (MFMA flash attention, bf16
+// 32 queries of one row and one KV head (MFMA flash attention, bf16
 // head_dim 64/128), or a block of queries on the vector ALU with K/V staged
 // in LDS as fp32.
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "common.h"
 #include "kernels.h"
@@ -62,6 +63,7 @@ __device__ __forceinline__ float group_sum(float d) {
   }
 }
 
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 typedef short i16x8 __attribute__((ext_vector_type(8)));
 
@@ -71,6 +73,46 @@ typedef short i16x8 __attribute__((ext_vector_type(8)));
 __device__ __forceinline__ i16x4 lds_read_tr16(const bf16_t* p) {
   return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4*)(p));
 }
+// LDS byte address of a shared-memory pointer.
+__device__ __forceinline__ uint32_t lds_addr(const bf16_t* p) {
+  return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const bf16_t*)(p);
+}
+// Transpose reads at byte offsets LO and HI from each of N LDS addresses,
+// complete on return (issue and wait are one block).  Unlike the builtin,
+// after which the compiler waits for every copy into LDS still in flight
+// (vmcnt 0), they leave the next tile's copies flying.
+template <int N, int LO, int HI>
+__device__ __forceinline__ void lds_read_tr16_pairs(const uint32_t (&a)[N], i16x4 (&lo)[N], i16x4 (&hi)[N]) {
+  static_assert(N == 2 || N == 4 || N == 8, "pairs");
+  if constexpr (N == 2) {
+    asm volatile(
+        "ds_read_b64_tr_b16 %0, %4 offset:%6\n\tds_read_b64_tr_b16 %1, %4 offset:%7\n\t"
+        "ds_read_b64_tr_b16 %2, %5 offset:%6\n\tds_read_b64_tr_b16 %3, %5 offset:%7\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : "=&v"(lo[0]), "=&v"(hi[0]), "=&v"(lo[1]), "=&v"(hi[1])
+        : "v"(a[0]), "v"(a[1]), "n"(LO), "n"(HI)
+        : "memory");
+  } else if constexpr (N == 4) {
+    asm volatile(
+        "ds_read_b64_tr_b16 %0, %8 offset:%12\n\tds_read_b64_tr_b16 %1, %8 offset:%13\n\t"
+        "ds_read_b64_tr_b16 %2, %9 offset:%12\n\tds_read_b64_tr_b16 %3, %9 offset:%13\n\t"
+        "ds_read_b64_tr_b16 %4, %10 offset:%12\n\tds_read_b64_tr_b16 %5, %10 offset:%13\n\t"
+        "ds_read_b64_tr_b16 %6, %11 offset:%12\n\tds_read_b64_tr_b16 %7, %11 offset:%13\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : "=&v"(lo[0]), "=&v"(hi[0]), "=&v"(lo[1]), "=&v"(hi[1]), "=&v"(lo[2]), "=&v"(hi[2]), "=&v"(lo[3]),
+          "=&v"(hi[3])
+        : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "n"(LO), "n"(HI)
+        : "memory");
+  }
+}
+
+// the value of lane l ^ 32
+__device__ __forceinline__ float other_half(float v) {
+  const uint32_t u = __float_as_uint(v);
+  const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  return __uint_as_float((threadIdx.x & 32) ? r[0] : r[1]);
+}
+
 // two transpose reads as one MFMA operand (the 16-bit words reinterpreted
 // as a whole vector)
 __device__ __forceinline__ bf16x8 tr16_pair(i16x4 lo, i16x4 hi) {
@@ -872,12 +914,179 @@ static int decode_kps(int rows, int hkv, int keys) {
 // Waves decode_wave_kernel aims at over the whole grid.
 constexpr int kWaveTarget = 2048;
 
-template <int HD, int G, bool PREFIX_ONLY, int QB>
-__global__ void prefill_attn_mfma_kernel(const float* __restrict__ q, const bf16_t* __restrict__ kpre,
-                                         const bf16_t* __restrict__ vpre, int P, const bf16_t* __restrict__ kown,
-                                         const bf16_t* __restrict__ vown, int rows, int lr, int cap, int t0, int hq,
-                                         int hkv, bf16_t* __restrict__ out, float qscale,
-                                         float* __restrict__ part, int part_splits);
+// The decode rows' attention over the shared prompt prefix (one query head
+// per KV head, 128 or more rows): a work-group of one wave takes 16 decode
+// rows of one head as the queries of
+//   S^T = K Q^T   (v_mfma_f32_16x16x32_bf16; lane l holds keys 4 (l / 16) + i
+//                 and 16 on of row l % 16), then
+//   O^T += V^T P^T, the key order permuted so that the B operand is the lane's
+//                 own probabilities, the A operand by two LDS transpose reads
+//                 of the staged V tile.
+// Every prefix key is visible.  32-key tiles, the next one fetched into
+// registers under the current one.  The tails were attended first and left
+// part_splits partial slots per (row, query head) in `part` (unnormalised
+// output, running max, sum); they are folded in by log-sum-exp and the
+// attention output is written.
+template <int HD, int G>
+__global__ void __launch_bounds__(64 * G)
+prefix_attn_mfma_kernel(const float* __restrict__ q, const bf16_t* __restrict__ kpre, const bf16_t* __restrict__ vpre,
+                        int P, int rows, int hq, bf16_t* __restrict__ out, float qscale,
+                        const float* __restrict__ part, int part_splits) {
+  constexpr int NT = 64 * G;
+  constexpr int KT = 32;             // keys per staged tile
+  constexpr int KS = HD / 32, DT = HD / 16, CPK = HD / 8;
+  constexpr int PF_KROW = HD + 8;    // K tile row (bf16), padded
+  constexpr int PF_VROW = HD + 16;   // V tile row (bf16), padded: the 8-byte transpose reads of a
+                                     // half wave (eight rows) fall on distinct banks
+  static_assert(HD == 64 || HD == 128, "head_dim");
+  __shared__ __attribute__((aligned(16))) bf16_t Ks[KT * PF_KROW];
+  __shared__ __attribute__((aligned(16))) bf16_t Vs[KT * PF_VROW];
+  const int h = blockIdx.y;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int fr = lane & 15, fg = lane >> 4;
+  const int qh = h * G + wave;
+  const int t = blockIdx.x * 16 + fr;      // this lane's decode row
+  const bool qvalid = t < rows;
+  // Q^T fragments: lane holds Q[t][32 s + 8 fg .. +8] for k-step s (scaled,
+  // bf16); loaded from a clamped row, unconditionally, so all go out at once
+  bf16x8 qf[KS];
+  {
+    const float sc = qvalid ? qscale : 0.f;
+    const float4* qr = reinterpret_cast<const float4*>(q + ((int64_t)min(t, rows - 1) * hq + qh) * HD);
+    float4 qv[2 * KS];
+#pragma unroll
+    for (int st = 0; st < KS; ++st) {
+      qv[2 * st] = qr[8 * st + 2 * fg];
+      qv[2 * st + 1] = qr[8 * st + 2 * fg + 1];
+    }
+#pragma unroll
+    for (int st = 0; st < KS; ++st) {
+      const float4 a = qv[2 * st], b = qv[2 * st + 1];
+      qf[st][0] = (__bf16)(a.x * sc); qf[st][1] = (__bf16)(a.y * sc);
+      qf[st][2] = (__bf16)(a.z * sc); qf[st][3] = (__bf16)(a.w * sc);
+      qf[st][4] = (__bf16)(b.x * sc); qf[st][5] = (__bf16)(b.y * sc);
+      qf[st][6] = (__bf16)(b.z * sc); qf[st][7] = (__bf16)(b.w * sc);
+    }
+  }
+  f32x4 o[DT];
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m = -INFINITY, l = 0.f;
+  const bf16_t* kp = kpre + (int64_t)h * P * HD;
+  const bf16_t* vp = vpre + (int64_t)h * P * HD;
+  // a tile is 32 keys x CPK chunks of 8 dims; thread chunks c = tid + NT i
+  constexpr int CPT = (KT * CPK + NT - 1) / NT;
+  uint4 kreg[CPT], vreg[CPT];
+  auto fetch = [&](int kb) {
+#pragma unroll
+    for (int i = 0; i < CPT; ++i) {
+      const int c = threadIdx.x + NT * i;
+      const int key = kb + c / CPK, cc = c % CPK;
+      kreg[i] = vreg[i] = make_uint4(0, 0, 0, 0);
+      if (c < KT * CPK && key < P) {
+        kreg[i] = *reinterpret_cast<const uint4*>(kp + (int64_t)key * HD + cc * 8);
+        vreg[i] = *reinterpret_cast<const uint4*>(vp + (int64_t)key * HD + cc * 8);
+      }
+    }
+  };
+  // Lane i of a group names dims dt 16 + 4 (i & 3) .. + 3 of key
+  // 4 fg + (i >> 2) (and 16 keys on), so it receives dim dt 16 + i of keys
+  // 4 fg .. + 3 (and 16 + 4 fg .. + 3): the A operand rows of O^T += V^T P^T
+  const bf16_t* vb0 = &Vs[(4 * fg + (fr >> 2)) * PF_VROW + 4 * (fr & 3)];
+  // the staged tile's keys kb .. kb + 31
+  auto compute = [&](int kb) {
+    // S^T for key tiles 0 (keys kb..kb+15) and 1 (kb+16..kb+31)
+    f32x4 st[2];
+#pragma unroll
+    for (int kt = 0; kt < 2; ++kt) {
+      st[kt] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int s = 0; s < KS; ++s) {
+        const bf16x8 kf = *reinterpret_cast<const bf16x8*>(&Ks[(kt * 16 + fr) * PF_KROW + 32 * s + 8 * fg]);
+        st[kt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qf[s], st[kt], 0, 0, 0);
+      }
+    }
+    // tile maximum for row t (this lane's column)
+    float mt = -INFINITY;
+#pragma unroll
+    for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int key = kb + kt * 16 + 4 * fg + i;
+        const bool ok = qvalid && key < P;
+        st[kt][i] = ok ? st[kt][i] : -INFINITY;
+        mt = fmaxf(mt, st[kt][i]);
+      }
+    mt = fmaxf(mt, __shfl_xor(mt, 16, 64));
+    mt = fmaxf(mt, __shfl_xor(mt, 32, 64));
+    const float mn = fmaxf(m, mt);
+    const float corr = (mn == -INFINITY) ? 1.f : exp2_or_zero(m - mn);
+    float ls = 0.f;
+    bf16x8 pf;
+#pragma unroll
+    for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float p = (mn == -INFINITY) ? 0.f : exp2_or_zero(st[kt][i] - mn);
+        ls += p;
+        pf[kt * 4 + i] = (__bf16)p;
+      }
+    ls += __shfl_xor(ls, 16, 64);
+    ls += __shfl_xor(ls, 32, 64);
+    l = l * corr + ls;
+    m = mn;
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) {
+      o[dt] *= corr;
+      const i16x4 lo = lds_read_tr16(vb0 + dt * 16);
+      const i16x4 hi = lds_read_tr16(vb0 + 16 * PF_VROW + dt * 16);
+      o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tr16_pair(lo, hi), pf, o[dt], 0, 0, 0);
+    }
+  };
+  fetch(0);
+  for (int kb = 0; kb < P; kb += KT) {
+    // stage K [key][dim] and V [key][dim]
+#pragma unroll
+    for (int i = 0; i < CPT; ++i) {
+      const int c = threadIdx.x + NT * i;
+      if (KT * CPK % NT == 0 || c < KT * CPK) {
+        const int j = c / CPK, cc = c % CPK;
+        *reinterpret_cast<uint4*>(&Ks[j * PF_KROW + cc * 8]) = kreg[i];
+        *reinterpret_cast<uint4*>(&Vs[j * PF_VROW + cc * 8]) = vreg[i];
+      }
+    }
+    lds_barrier();
+    if (kb + KT < P) fetch(kb + KT);
+    compute(kb);
+    lds_barrier();
+  }
+  if (qvalid) {
+    // fold in the tail partials of (row t, head qh): slot s holds the
+    // unnormalised output, its maximum and its sum
+    const float* pr = part + ((int64_t)t * hq + qh) * part_splits * (HD + 2);
+    float mx = m;
+    for (int sp = 0; sp < part_splits; ++sp) mx = fmaxf(mx, pr[sp * (HD + 2) + HD]);
+    const float c0 = exp2_or_zero(m - mx);
+    float L = l * c0;
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) o[dt] *= c0;
+    for (int sp = 0; sp < part_splits; ++sp) {
+      const float* ps = pr + sp * (HD + 2);
+      const float cs = exp2_or_zero(ps[HD] - mx);
+      L += ps[HD + 1] * cs;
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) o[dt][i] += ps[dt * 16 + 4 * fg + i] * cs;
+    }
+    const float inv = 1.0f / L;
+    bf16_t* orow = out + ((int64_t)t * hq + qh) * HD;
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) orow[dt * 16 + 4 * fg + i] = f32_to_bf16(o[dt][i] * inv);
+  }
+}
 
 // Whether the shared prefix is attended by the batched MFMA kernel (from 128
 // rows; below that it costs more than the L2 reads it saves).
@@ -985,9 +1194,8 @@ static void launch_decode(const DecodeAttnArgs& a, hipStream_t s) {
   // runs last: the tails leave partial slots and it folds them into its own
   // result, so no merge pass is needed.
   auto prefix_pass = [&](int tsplits) {
-    SR_LAUNCH((prefill_attn_mfma_kernel<128, G, true, 1>), dim3((a.rows + 15) / 16, a.hkv, 1), dim3(64 * G), 0, s,
-                       a.q, (const bf16_t*)a.kpre, (const bf16_t*)a.vpre, a.P, nullptr, nullptr, 1, a.rows, 0, 0, a.hq,
-                       a.hkv, (bf16_t*)a.out, qscale, a.part, tsplits);
+    SR_LAUNCH((prefix_attn_mfma_kernel<128, G>), dim3((a.rows + 15) / 16, a.hkv), dim3(64 * G), 0, s, a.q,
+              (const bf16_t*)a.kpre, (const bf16_t*)a.vpre, a.P, a.rows, a.hq, (bf16_t*)a.out, qscale, a.part, tsplits);
     SR_CHECK_LAUNCH();
   };
   if constexpr ((HD == 64 || HD == 128) && (G == 2 || G == 4 || G == 8)) {
@@ -1242,230 +1450,297 @@ prefill_attn_kernel(const float* __restrict__ q, const T* __restrict__ kpre, con
 
 
 // --------------------------------------------------------- prefill (MFMA)
-// bf16 flash attention with v_mfma_f32_16x16x32_bf16, head_dim 64 or 128.
-// Work-group = one row, one KV head, QB blocks of 16 queries; wave w
-// computes query head (kvh * G + w % G) for query block w / G, so the G QB
-// waves share every K/V tile staged in LDS.  (Two or four 16-query
-// blocks per wave instead reuse a tile more but hold too many registers for
-// more than one or two work-groups per SIMD, and measured slower.)
-//   S^T = K Q^T   (keys x queries): lane l holds keys 4(l/16)+i (+16 for the
-//                 second key tile) of query l%16, so the online-softmax state
-//                 of a query lives in one lane group (max/sum over l/16).
-//   O^T += V^T P^T (dims x queries): the key order of this contraction is
-//                 permuted so that the B operand is exactly the lane's own
-//                 S^T values (keys 4g..4g+3 of tile 0, then of tile 1); the A
-//                 operand comes from the V tile, staged row by row like K, by
-//                 two LDS transpose reads.
-// Tiles of 64 keys (32 in the prefix pass) staged in LDS, computed 32 keys
-// at a time; the next tile is fetched into registers while the current one
-// is computed.
-constexpr int PF_KT = 64;            // keys per staged tile (prefill form)
+// bf16 flash attention with v_mfma_f32_32x32x16_bf16, head_dim 64 or 128.
+// Work-group = one row, one KV head, QB blocks of 32 queries; wave w computes
+// query head (kvh * G + w % G) for query block w / G, so the G QB waves share
+// every staged K/V tile.
+//   S^T = K Q^T   (keys x queries): lane l holds, of every 32 keys, the 16
+//                 with (key / 4) % 2 = l / 32 for query l % 32, so a query's
+//                 softmax state lives in lanes l and l + 32.
+//   O^T += V^T P^T (dims x queries): the contraction visits the keys of a
+//                 16-key chunk in the order the lane holds them (0-3 and 8-11
+//                 of it for l < 32, 4-7 and 12-15 for the others), so the B
+//                 operand is the lane's own eight probabilities; the A operand
+//                 comes from the V tile by two LDS transpose reads.
+// KT-key tiles go memory -> LDS by global_load_lds, four stages deep, one
+// barrier per tile; the scores of the next 32 keys are formed under the
+// probabilities of these; 16-byte chunks sit XOR-swizzled in the LDS rows (K:
+// the fragment reads of eight neighbouring keys, V: the transpose reads of a
+// half wave, on distinct banks).  Queries and outputs pass through LDS too, so
+// that memory sees whole rows.  Online softmax in base 2; the running maximum
+// a column is scaled by moves only when 32 keys exceed it by more than 2^8 in
+// some column, so most leave the 64 accumulators alone (probabilities, sum
+// and output stay fp32 multiples of the same scale).
+// Four waves and 32-key tiles, two work-groups a CU (eight waves and 64-key
+// tiles with 8 query heads a KV head): eight waves in one work-group were
+// 5-17 % slower on short responses and at head_dim 64.
+// Against 16-query waves with tiles staged through registers, head_dim 128:
+// 103 rows x 32 heads x 507 queries after 384 keys 1136 -> 798 us, 512 rows
+// of 128 queries after 256 keys 833 -> 632 us (3 TB/s of queries, outputs and
+// keys), one prompt of 256 15.5 -> 11.4 us.  What is left is issue: VALU
+// (16 exponentials of 32 keys take as long as half their MFMAs), MFMA and LDS
+// waits overlap only across the two waves of a SIMD.
+constexpr int PF_NST = 4;            // stages
+constexpr float PF_LAZY = 8.0f;      // log2 of the growth that moves the maximum
 
-// PREFIX_ONLY: the decode rows' attention over the shared prompt prefix.
-// The 16 "queries" of a work-group are 16 decode rows (lr = rows, one
-// sequence) and every prefix key is visible.  The tails were attended first
-// and left part_splits partial slots per (row, query head) in `part`
-// (unnormalised output, running max, sum); the work-group folds them into
-// its own result by log-sum-exp and writes the attention output.
-template <int HD, int G, bool PREFIX_ONLY, int QB>
-__global__ void __launch_bounds__(64 * G * QB)
+template <int HD, int G, int QB, int KT>
+__global__ void __launch_bounds__(64 * G * QB, 2)
 prefill_attn_mfma_kernel(const float* __restrict__ q, const bf16_t* __restrict__ kpre,
                          const bf16_t* __restrict__ vpre, int P, const bf16_t* __restrict__ kown,
                          const bf16_t* __restrict__ vown, int rows, int lr, int cap, int t0, int hq, int hkv,
-                         bf16_t* __restrict__ out, float qscale, float* __restrict__ part, int part_splits) {
-  constexpr int NT = 64 * G * QB;
-  static_assert(!PREFIX_ONLY || QB == 1, "the prefix pass takes one query block per work-group");
-  // keys per staged tile: 64 for the prefill form (its work-groups have
-  // eight waves to fetch them), 32 for the prefix pass (G waves)
-  constexpr int KT = PREFIX_ONLY ? 32 : PF_KT;
-  constexpr int KS = HD / 32, DT = HD / 16, CPK = HD / 8;
-  constexpr int PF_KROW = HD + 8;    // K tile row (bf16), padded
-  constexpr int PF_VROW = HD + 16;   // V tile row (bf16), padded: the 8-byte transpose reads of a
-                                     // half wave (eight rows) fall on distinct banks
+                         bf16_t* __restrict__ out, float qscale) {
+  constexpr int NW = G * QB;
+  constexpr int KS = HD / 16, DT = HD / 32, CPK = HD / 8;
+  constexpr int TILE = KT * HD;                // bf16 elements of a K (or V) tile
+  constexpr int RPI = 64 / CPK;                // keys per copy instruction (1 KB)
+  constexpr int DPW = KT / RPI / NW;        // copies per wave of a K (or V) tile
   static_assert(HD == 64 || HD == 128, "head_dim");
-  __shared__ __attribute__((aligned(16))) bf16_t Ks[KT * PF_KROW];
-  __shared__ __attribute__((aligned(16))) bf16_t Vs[KT * PF_VROW];
-  // The prefill form runs a 1-D grid of 8 C work-groups, dealt round-robin
-  // to the 8 XCDs: XCD x takes the consecutive logical blocks
-  // [x C, (x + 1) C), ordered query block fastest, so the query blocks that
+  static_assert(DPW * RPI * NW == KT, "copies divide the tile");
+  __shared__ __attribute__((aligned(1024))) bf16_t lds[PF_NST * 2 * TILE];
+  // A 1-D grid of 8 C work-groups, dealt round-robin to the 8 XCDs: XCD x
+  // takes the consecutive logical blocks [x C, (x + 1) C), ordered query
+  // block fastest (last block, the longest, first), so the query blocks that
   // read the same row's keys share one L2.
-  int qb0, h, row;
-  if constexpr (PREFIX_ONLY) {
-    qb0 = blockIdx.x;
-    h = blockIdx.y;
-    row = 0;
-  } else {
-    const int ngq = ((lr + 15) / 16 + QB - 1) / QB, total = ngq * hkv * rows;
-    const int per_xcd = (total + 7) / 8;
-    const int pid = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
-    if (pid >= total) return;
-    qb0 = (pid % ngq) * QB;
-    h = (pid / ngq) % hkv;
-    row = pid / (ngq * hkv);
-  }
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int fr = lane & 15, fg = lane >> 4;
-  // wave w: query head h G + w % G of query block qb0 + w / G (the QB
-  // blocks of a work-group share every staged K/V tile)
-  const int qb = qb0 + wave / G;
+  const int ngq = (lr + 32 * QB - 1) / (32 * QB), total = ngq * hkv * rows;
+  const int per_xcd = (total + 7) / 8;
+  const int pid = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+  if (pid >= total) return;
+  const int qg = ngq - 1 - pid % ngq;
+  const int h = (pid / ngq) % hkv;
+  const int row = pid / (ngq * hkv);
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int fr = lane & 31, fh = lane >> 5;
+  const int b0 = (qg * QB + wave / G) * 32;     // first query of the wave
   const int qh = h * G + wave % G;
-  const int t = qb * 16 + fr;              // this lane's query (as B column / C column)
-  const bool qvalid = t < lr;
-  // Q^T fragments: lane holds Q[t][32 s + 8 fg .. +8] for k-step s (scaled,
-  // bf16); loaded from a clamped row, unconditionally, so all go out at once
-  bf16x8 qf[KS];
-  {
-    const float sc = qvalid ? qscale : 0.f;
-    const float4* qr = reinterpret_cast<const float4*>(q + (((int64_t)row * lr + min(t, lr - 1)) * hq + qh) * HD);
-    float4 qv[2 * KS];
+  const int t = b0 + fr;                        // this lane's query
+  const int nkeys = P + t0 + min(lr, (qg + 1) * QB * 32);           // of the work-group's last query
+  const int wkeys = b0 < lr ? P + t0 + min(lr, b0 + 32) : 0;        // of this wave's
+  const int ntile = (nkeys + KT - 1) / KT;
+
+  // The wave's 32 query rows, 16 bytes per lane along whole rows (from
+  // clamped rows; results of rows past the end are not stored)
+  constexpr int LPR = HD / 4, RPQ = 64 / LPR, NQ = 32 / RPQ;   // lanes per row, rows per load, loads
+  float4 qv[NQ];
 #pragma unroll
-    for (int st = 0; st < KS; ++st) {
-      qv[2 * st] = qr[8 * st + 2 * fg];
-      qv[2 * st + 1] = qr[8 * st + 2 * fg + 1];
-    }
-#pragma unroll
-    for (int st = 0; st < KS; ++st) {
-      const float4 a = qv[2 * st], b = qv[2 * st + 1];
-      qf[st][0] = (__bf16)(a.x * sc); qf[st][1] = (__bf16)(a.y * sc);
-      qf[st][2] = (__bf16)(a.z * sc); qf[st][3] = (__bf16)(a.w * sc);
-      qf[st][4] = (__bf16)(b.x * sc); qf[st][5] = (__bf16)(b.y * sc);
-      qf[st][6] = (__bf16)(b.z * sc); qf[st][7] = (__bf16)(b.w * sc);
-    }
+  for (int i = 0; i < NQ; ++i) {
+    const int tq = min(b0 + RPQ * i + lane / LPR, lr - 1);
+    qv[i] = reinterpret_cast<const float4*>(q + (((int64_t)row * lr + tq) * hq + qh) * HD)[lane % LPR];
   }
-  f32x4 o[DT];
-#pragma unroll
-  for (int dt = 0; dt < DT; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float m = -INFINITY, l = 0.f;
-  // keys of the work-group's last query (its waves' masks cut the rest)
-  const int tlast = min(lr, (qb0 + QB) * 16) - 1;
-  const int nkeys = PREFIX_ONLY ? P : P + t0 + tlast + 1;
+
+  // Copies: instruction i of a wave moves keys RPI (wave + NW i) .. of the
+  // tile; lane l writes slot l % CPK of key l / CPK and fetches the chunk
+  // stored there.  Keys past the last are clamped (their scores are masked).
   const bf16_t* kp = kpre + (int64_t)h * P * HD;
   const bf16_t* vp = vpre + (int64_t)h * P * HD;
-  const bf16_t* ko = PREFIX_ONLY ? kp : kown + ((int64_t)row * hkv + h) * cap * HD;
-  const bf16_t* vo = PREFIX_ONLY ? vp : vown + ((int64_t)row * hkv + h) * cap * HD;
-  // a tile is 32 keys x CPK chunks of 8 dims; thread chunks c = tid + NT i
-  constexpr int CPT = (KT * CPK + NT - 1) / NT;
-  uint4 kreg[CPT], vreg[CPT];
-  auto fetch = [&](int kb) {
+  const bf16_t* ko = kown + ((int64_t)row * hkv + h) * cap * HD;
+  const bf16_t* vo = vown + ((int64_t)row * hkv + h) * cap * HD;
+  auto vswz = [](int k) { return HD == 128 ? (k & 3) << 2 : ((k >> 1) & 1) << 2; };
+  auto issue = [&](int tile, int buf) {
+    bf16_t* kd = lds + buf * 2 * TILE;
+    bf16_t* vd = kd + TILE;
 #pragma unroll
-    for (int i = 0; i < CPT; ++i) {
-      const int c = threadIdx.x + NT * i;
-      const int key = kb + c / CPK, cc = c % CPK;
-      kreg[i] = vreg[i] = make_uint4(0, 0, 0, 0);
-      if (c < KT * CPK && key < nkeys) {
-        const bf16_t* kr = key < P ? kp + (int64_t)key * HD : ko + (int64_t)(key - P) * HD;
-        const bf16_t* vr = key < P ? vp + (int64_t)key * HD : vo + (int64_t)(key - P) * HD;
-        kreg[i] = *reinterpret_cast<const uint4*>(kr + cc * 8);
-        vreg[i] = *reinterpret_cast<const uint4*>(vr + cc * 8);
-      }
+    for (int i = 0; i < DPW; ++i) {
+      const int r0 = RPI * (wave + NW * i);
+      const int r = r0 + lane / CPK, sl = lane % CPK;
+      const int j = min(tile * KT + r, nkeys - 1);
+      const int64_t off = (int64_t)(j < P ? j : j - P) * HD;
+      dma16(reinterpret_cast<const char*>((j < P ? kp : ko) + off + 8 * (sl ^ (r & (CPK - 1)))), kd + r0 * HD);
+      dma16(reinterpret_cast<const char*>((j < P ? vp : vo) + off + 8 * (sl ^ vswz(r))), vd + r0 * HD);
     }
   };
-  // Lane i of a group names dims dt 16 + 4 (i & 3) .. + 3 of key
-  // 4 fg + (i >> 2) (and 16 keys on), so it receives dim dt 16 + i of keys
-  // 4 fg .. + 3 (and 16 + 4 fg .. + 3): the A operand rows of O^T += V^T P^T
-  const bf16_t* vb0 = &Vs[(4 * fg + (fr >> 2)) * PF_VROW + 4 * (fr & 3)];
-  // the staged tile's keys kb .. kb + 31, at tile row r0
-  auto compute = [&](int kb, int r0) {
-    const bf16_t* vb = vb0 + r0 * PF_VROW;
-    // S^T for key tiles 0 (keys kb..kb+15) and 1 (kb+16..kb+31)
-    f32x4 st[2];
-#pragma unroll
-    for (int kt = 0; kt < 2; ++kt) {
-      st[kt] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int s = 0; s < KS; ++s) {
-        const bf16x8 kf = *reinterpret_cast<const bf16x8*>(&Ks[(r0 + kt * 16 + fr) * PF_KROW + 32 * s + 8 * fg]);
-        st[kt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qf[s], st[kt], 0, 0, 0);
-      }
-    }
-    // causal mask and tile maximum for query t (this lane's column)
-    float mt = -INFINITY;
-#pragma unroll
-    for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int key = kb + kt * 16 + 4 * fg + i;
-        const bool ok = qvalid && key < nkeys && (PREFIX_ONLY || key <= P + t0 + t);
-        st[kt][i] = ok ? st[kt][i] : -INFINITY;
-        mt = fmaxf(mt, st[kt][i]);
-      }
-    mt = fmaxf(mt, __shfl_xor(mt, 16, 64));
-    mt = fmaxf(mt, __shfl_xor(mt, 32, 64));
-    const float mn = fmaxf(m, mt);
-    const float corr = (mn == -INFINITY) ? 1.f : exp2_or_zero(m - mn);
-    float ls = 0.f;
-    bf16x8 pf;
-#pragma unroll
-    for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float p = (mn == -INFINITY) ? 0.f : exp2_or_zero(st[kt][i] - mn);
-        ls += p;
-        pf[kt * 4 + i] = (__bf16)p;
-      }
-    ls += __shfl_xor(ls, 16, 64);
-    ls += __shfl_xor(ls, 32, 64);
-    l = l * corr + ls;
-    m = mn;
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt) {
-      o[dt] *= corr;
-      const i16x4 lo = lds_read_tr16(vb + dt * 16);
-      const i16x4 hi = lds_read_tr16(vb + 16 * PF_VROW + dt * 16);
-      o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tr16_pair(lo, hi), pf, o[dt], 0, 0, 0);
-    }
+  auto wait_barrier = [](auto n) {
+    constexpr int N = decltype(n)::value;
+    if constexpr (N == 0) asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    else if constexpr (N == 2) asm volatile("s_waitcnt vmcnt(2) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    else if constexpr (N == 4) asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    else if constexpr (N == 8) asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    else static_assert(N < 0, "add this wait count");
   };
-  fetch(0);
-  for (int kb = 0; kb < nkeys; kb += KT) {
-    // stage K [key][dim] and V [key][dim]
+
+  // LDS element offsets: the K fragment of key fr (chunk 2 s + fh), and the
+  // four dims dt 32 + 16 (l / 16 % 2) + 4 (l % 4) .. of V key 4 fh + l % 16 / 4
+  bf16x8 qf[KS];
+  int koff[KS];
+  uint32_t vbase[DT];   // LDS bytes, in the first stage's V tile
 #pragma unroll
-    for (int i = 0; i < CPT; ++i) {
-      const int c = threadIdx.x + NT * i;
-      if (KT * CPK % NT == 0 || c < KT * CPK) {
-        const int j = c / CPK, cc = c % CPK;
-        *reinterpret_cast<uint4*>(&Ks[j * PF_KROW + cc * 8]) = kreg[i];
-        *reinterpret_cast<uint4*>(&Vs[j * PF_VROW + cc * 8]) = vreg[i];
-      }
-    }
-    lds_barrier();
-    if (kb + KT < nkeys) fetch(kb + KT);
-    compute(kb, 0);
-    if (KT == 64 && kb + 32 < nkeys) compute(kb + 32, 32);
-    lds_barrier();
+  for (int s = 0; s < KS; ++s) koff[s] = fr * HD + 8 * ((2 * s + fh) ^ (fr & (CPK - 1)));
+  {
+    const int vk = 4 * fh + ((lane & 15) >> 2);
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+      vbase[dt] = lds_addr(lds + TILE + vk * HD +
+                           8 * ((4 * dt + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) ^ vswz(vk)) + 4 * (lane & 1));
   }
-  if (qvalid) {
-    if (PREFIX_ONLY) {
-      // fold in the tail partials of (row t, head qh): slot s holds the
-      // unnormalised output, its maximum and its sum
-      const float* pr = part + ((int64_t)t * hq + qh) * part_splits * (HD + 2);
-      float mx = m;
-      for (int sp = 0; sp < part_splits; ++sp) mx = fmaxf(mx, pr[sp * (HD + 2) + HD]);
-      const float c0 = exp2_or_zero(m - mx);
-      float L = l * c0;
+
+  f32x16 o[DT];
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt) o[dt] *= c0;
-      for (int sp = 0; sp < part_splits; ++sp) {
-        const float* ps = pr + sp * (HD + 2);
-        const float cs = exp2_or_zero(ps[HD] - mx);
-        L += ps[HD + 1] * cs;
+  for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
+    for (int e = 0; e < 16; ++e) o[dt][e] = 0.f;
+  float m = -INFINITY, l = 0.f;
+
+  auto zero = [](f32x16& sc) {
 #pragma unroll
-          for (int i = 0; i < 4; ++i) o[dt][i] += ps[dt * 16 + 4 * fg + i] * cs;
+    for (int e = 0; e < 16; ++e) sc[e] = 0.f;
+  };
+  // Half a tile: the scores `sc` of the 32 keys from `key` on are there (V
+  // rows from byte VOFF of the V tile); the scores of the next 32 keys (K rows
+  // at `kn`) are formed into `sn`.  Per 16-key chunk: the K fragments and V
+  // of the chunk are read under the O MFMAs of the chunk before, then every
+  // score MFMA runs beside a share of the chunk's probabilities.
+  constexpr int KC = KS / 2;     // score MFMAs of a chunk
+  auto half = [&](auto voff, int key, const uint32_t (&va)[DT], const bf16_t* kn, f32x16& sc, f32x16& sn) {
+    constexpr int VOFF = decltype(voff)::value;
+    bf16x8 kf[KC], pf;
+    i16x4 lo[DT], hi[DT];
+    auto read_k = [&](int c) {
+#pragma unroll
+      for (int s = 0; s < KC; ++s) kf[s] = *reinterpret_cast<const bf16x8*>(kn + koff[c * KC + s]);
+    };
+    auto scores = [&](int c) {
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int s = 0; s < KC; ++s) {
+        sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s], qf[c * KC + s], sn, 0, 0, 0);
+#pragma unroll
+        for (int e = s * 8 / KC; e < (s + 1) * 8 / KC; ++e) {
+          const float p = __builtin_amdgcn_exp2f(sc[8 * c + e] - m);
+          l += p;
+          pf[e] = (__bf16)p;
+        }
       }
-      const float inv = 1.0f / L;
-      bf16_t* orow = out + ((int64_t)t * hq + qh) * HD;
+#pragma unroll
+      for (int s = 0; s < KC; ++s) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, 8 / KC, 0);
+        __builtin_amdgcn_sched_group_barrier(0x400, 8 / KC, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, 12 / KC, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    auto output = [&] {
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt)
+        o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr16_pair(lo[dt], hi[dt]), pf, o[dt], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    read_k(0);
+    lds_read_tr16_pairs<DT, VOFF, VOFF + 8 * HD * 2>(va, lo, hi);
+    if (key + 31 > P + t0 + b0) {   // the diagonal (wave-uniform)
+      asm volatile("");             // (a branch, not 32 selects on every tile)
+      const int lim = P + t0 + t - key - 4 * fh;   // last visible key, from this lane's first
 #pragma unroll
-        for (int i = 0; i < 4; ++i) orow[dt * 16 + 4 * fg + i] = f32_to_bf16(o[dt][i] * inv);
+      for (int e = 0; e < 16; ++e)
+        if (8 * (e >> 2) + (e & 3) > lim) sc[e] = -INFINITY;
+    }
+    float mt = sc[0];
+#pragma unroll
+    for (int e = 1; e < 16; ++e) mt = fmaxf(mt, sc[e]);
+    mt = fmaxf(mt, other_half(mt));
+    if (__any(mt > m + PF_LAZY)) {
+      const float mn = fmaxf(m, mt);
+      const float corr = mn == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m - mn);
+      l *= corr;
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) o[dt] *= corr;
+      m = mn;
+    }
+    zero(sn);
+    scores(0);
+    read_k(1);
+    output();
+    lds_read_tr16_pairs<DT, VOFF + 16 * HD * 2, VOFF + 24 * HD * 2>(va, lo, hi);
+    scores(1);
+    output();
+  };
+  constexpr int CPW = 2 * DPW;   // copies per wave and tile
+  // Before tile i: tile i + 1 landed too (its first scores are formed under
+  // tile i; only the copies of i + 2 may still fly), and every wave is done
+  // with tile i - 1, whose buffer takes tile i + 3.
+  auto sync = [&](int tile) {
+    if (tile + 2 < ntile) wait_barrier(std::integral_constant<int, CPW>{});
+    else wait_barrier(std::integral_constant<int, 0>{});
+    if (tile + PF_NST - 1 < ntile) issue(tile + PF_NST - 1, (tile + PF_NST - 1) % PF_NST);
+  };
+  auto kstage = [&](int tile) { return lds + (tile % PF_NST) * 2 * TILE; };
+  auto vstage = [&](int tile, uint32_t (&va)[DT]) {
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) va[dt] = vbase[dt] + (uint32_t)(tile % PF_NST) * (2 * TILE * 2);
+  };
+  // Tiles 0 and 1 go out first; the scaled bf16 queries pass through the
+  // buffers of tiles 2 and 3 (a 32-row slice per wave, chunks placed like
+  // K's) into fragments: lane holds Q[t][16 s + 8 fh .. + 8].
+  issue(0, 0);
+  if (ntile > 1) issue(1, 1);
+  bf16_t* const slice = lds + wave * 32 * HD;
+  {
+    bf16_t* qs = slice + 2 * 2 * TILE;
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) {
+      const int r = RPQ * i + lane / LPR, c4 = lane % LPR;
+      const bf16x4 v = {(__bf16)(qv[i].x * qscale), (__bf16)(qv[i].y * qscale), (__bf16)(qv[i].z * qscale),
+                        (__bf16)(qv[i].w * qscale)};
+      *reinterpret_cast<bf16x4*>(qs + r * HD + 8 * ((c4 >> 1) ^ (r & (CPK - 1))) + 4 * (c4 & 1)) = v;
+    }
+#pragma unroll
+    for (int s = 0; s < KS; ++s) qf[s] = *reinterpret_cast<const bf16x8*>(qs + koff[s]);
+  }
+  f32x16 sa, sb;
+  zero(sa);
+  wait_barrier(std::integral_constant<int, 0>{});   // tiles 0 and 1, and every wave's queries read
+  if (ntile > 2) issue(2, 2);
+  if (ntile > 3) issue(3, 3);
+#pragma unroll
+  for (int s = 0; s < KS; ++s) {
+    const bf16x8 kf = *reinterpret_cast<const bf16x8*>(lds + koff[s]);
+    sa = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[s], sa, 0, 0, 0);
+  }
+  // 64 keys a round; the scores formed past the last tile are those of a
+  // stale buffer and never used
+  for (int kb = 0, tile = 0; kb < nkeys; kb += 64) {
+    if (kb > 0) sync(tile);
+    uint32_t va[DT];
+    if (kb < wkeys) {   // else beyond this wave's last query
+      vstage(tile, va);
+      half(std::integral_constant<int, 0>{}, kb, va, KT == 64 ? kstage(tile) + 32 * HD : kstage(tile + 1), sa, sb);
+    }
+    if constexpr (KT == 32) {
+      ++tile;
+      if (tile < ntile) sync(tile);
+    }
+    if (kb + 32 < wkeys) {
+      if constexpr (KT == 32) vstage(tile, va);
+      half(std::integral_constant<int, KT == 64 ? 32 * HD * 2 : 0>{}, kb + 32, va, kstage(tile + 1), sb, sa);
+    }
+    ++tile;
+  }
+  l += other_half(l);
+  const float inv = 1.0f / l;
+  wait_barrier(std::integral_constant<int, 0>{});   // every wave is done with the tiles
+  // The outputs pass through the wave's slice of LDS (chunks placed like
+  // K's), so that a row leaves as one contiguous run.
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const bf16x4 v = {(__bf16)(o[dt][4 * g] * inv), (__bf16)(o[dt][4 * g + 1] * inv),
+                        (__bf16)(o[dt][4 * g + 2] * inv), (__bf16)(o[dt][4 * g + 3] * inv)};
+      *reinterpret_cast<bf16x4*>(slice + fr * HD + 8 * ((4 * dt + g) ^ (fr & (CPK - 1))) + 4 * fh) = v;
+    }
+  const bool wide = (reinterpret_cast<uintptr_t>(out) & 15) == 0;
+#pragma unroll
+  for (int i = 0; i < 32 / RPI; ++i) {
+    const int r = RPI * i + lane / CPK, c = lane % CPK;
+    const uint4 v = *reinterpret_cast<const uint4*>(slice + r * HD + 8 * (c ^ (r & (CPK - 1))));
+    if (b0 + r >= lr) continue;
+    bf16_t* dst = out + (((int64_t)row * lr + b0 + r) * hq + qh) * HD + 8 * c;
+    if (wide) {
+      *reinterpret_cast<uint4*>(dst) = v;
     } else {
-      const float inv = 1.0f / l;
-      bf16_t* orow = out + (((int64_t)row * lr + t) * hq + qh) * HD;
+      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) orow[dt * 16 + 4 * fg + i] = f32_to_bf16(o[dt][i] * inv);
+      for (int k = 0; k < 8; ++k) dst[k] = (bf16_t)(w[k >> 1] >> (16 * (k & 1)));
     }
   }
 }
@@ -1502,19 +1777,16 @@ static void prefill_by_hd(const PrefillAttnArgs& a, hipStream_t s) {
   }
 }
 
-// Waves per prefill work-group: G query heads x QB query blocks of 16.
-constexpr int kPrefillWaves = 8;
-
 template <int HD, int G>
 static void launch_prefill_mfma(const PrefillAttnArgs& a, hipStream_t s) {
   const float qscale = kLog2e / sqrtf((float)HD);
-  constexpr int QB = kPrefillWaves / G;   // query blocks per work-group
-  const int64_t total = (int64_t)(((a.lr + 15) / 16 + QB - 1) / QB) * a.hkv * a.rows;
+  constexpr int QB = G <= 4 ? 4 / G : 1;   // query blocks per work-group
+  const int64_t total = (int64_t)((a.lr + 32 * QB - 1) / (32 * QB)) * a.hkv * a.rows;
   SR_REQUIRE(total <= (int64_t)INT32_MAX - 8, SR_ERR_UNSUPPORTED, "prefill attention grid too large");
   dim3 grid((unsigned)(8 * ((total + 7) / 8)));
-  SR_LAUNCH((prefill_attn_mfma_kernel<HD, G, false, QB>), grid, dim3(64 * G * QB), 0, s, a.q, (const bf16_t*)a.kpre,
-                     (const bf16_t*)a.vpre, a.P, (const bf16_t*)a.kown, (const bf16_t*)a.vown, a.rows, a.lr, a.cap,
-                     a.t0, a.hq, a.hkv, (bf16_t*)a.out, qscale, nullptr, 0);
+  SR_LAUNCH((prefill_attn_mfma_kernel<HD, G, QB, G <= 4 ? 32 : 64>), grid, dim3(64 * G * QB), 0, s, a.q,
+            (const bf16_t*)a.kpre, (const bf16_t*)a.vpre, a.P, (const bf16_t*)a.kown, (const bf16_t*)a.vown, a.rows,
+            a.lr, a.cap, a.t0, a.hq, a.hkv, (bf16_t*)a.out, qscale);
   SR_CHECK_LAUNCH();
 }
 

@@ -102,6 +102,15 @@ PREFILL_CASES = [
     ("bf16", 128, 16, 2, 2, 17, 0, 50, 64),
     ("bf16", 128, 32, 8, 1, 5, 0, 1, 1),
     ("bf16", 64, 8, 2, 3, 33, 20, 17, 40),
+    # edges of the 32-query blocks, of the 64-key tiles and of the eight-wave
+    # work-groups (256 or more of them), for every group size
+    ("bf16", 128, 32, 8, 1, 31, 0, 32, 32),
+    ("bf16", 128, 32, 8, 1, 0, 63, 33, 96),
+    ("bf16", 64, 16, 8, 1, 64, 0, 65, 65),
+    ("bf16", 128, 32, 8, 32, 33, 31, 64, 96),
+    ("bf16", 128, 16, 8, 33, 64, 0, 65, 70),
+    ("bf16", 64, 8, 8, 34, 3, 62, 63, 130),
+    ("bf16", 64, 32, 4, 40, 127, 1, 70, 71),
     ("f32", 32, 4, 4, 2, 5, 9, 11, 20),
     ("f32", 64, 8, 2, 1, 0, 0, 1, 1),
     ("f32", 32, 8, 1, 2, 3, 64, 40, 110),
@@ -142,3 +151,32 @@ def test_prefill_attention(dtype, hd, hq, hkv, rows, P, t0, lr, cap):
         worst = max(worst, float(np.abs(got[r] - ref).max() / np.abs(ref).max()))
     tol = 1e-2 if bf16 else 1e-5
     assert worst <= tol, worst
+
+
+@pytest.mark.parametrize("hd,hq,hkv,rows,P,t0,lr", [(64, 8, 2, 9, 128, 0, 37), (128, 32, 8, 1, 0, 0, 20),
+                                                    (128, 16, 8, 3, 1, 2, 30), (64, 32, 8, 40, 70, 0, 33),
+                                                    (128, 64, 8, 5, 90, 0, 70)])
+def test_prefill_attention_after_nans(hd, hq, hkv, rows, P, t0, lr):
+    """A call whose keys and values are all NaN leaves them in LDS; the next
+    call reads none of them (keys past the last one, stages never filled)."""
+    torch, sr = need_gpu()
+    say(f"prefill after NaN hd={hd} hq={hq} hkv={hkv} rows={rows} P={P} t0={t0} lr={lr}")
+    bf = torch.bfloat16
+    nan = torch.full((64, 8, 192, 128), float("nan"), dtype=bf, device="cuda")
+    qn = torch.zeros((64, 192, 32, 128), dtype=torch.float32, device="cuda")
+    sr.prefill_attention(qn, None, None, nan, nan, 0, torch.empty((64, 192, 32 * 128), dtype=bf, device="cuda"))
+    g = torch.Generator(device="cuda").manual_seed(hd + lr)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda")
+    q = rnd(rows, lr, hq, hd)
+    kp, vp = (rnd(hkv, P, hd).to(bf), rnd(hkv, P, hd).to(bf)) if P else (None, None)
+    ko, vo = rnd(rows, hkv, t0 + lr, hd).to(bf), rnd(rows, hkv, t0 + lr, hd).to(bf)
+    out = torch.empty((rows, lr, hq * hd), dtype=bf, device="cuda")
+    sr.prefill_attention(q, kp, vp, ko, vo, t0, out)
+    got = out.double().cpu().numpy().reshape(rows, lr, hq, hd)
+    for r in range(rows):
+        k, v = (np.concatenate([([] if p is None else [p.double().cpu().numpy()]) + [o[r].double().cpu().numpy()]][0],
+                               axis=1).transpose(1, 0, 2) for p, o in ((kp, ko), (vp, vo)))
+        qf = np.zeros((P + t0 + lr, hq, hd))
+        qf[P + t0:] = q[r].double().cpu().numpy()
+        ref = causal_attention(qf, k, v, hkv)[P + t0:]
+        assert np.abs(got[r] - ref).max() <= 1e-2 * np.abs(ref).max()
