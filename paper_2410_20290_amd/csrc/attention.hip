@@ -308,11 +308,40 @@ __device__ __forceinline__ int vslot(int k, int c) {
   else return c ^ ((k & 3) << 1);
 }
 
-// Decode attention over keys [key0, P + lt) for bf16, head_dim 64 or 128,
-// on MFMA, with the keys split between the NW waves of a work-group (and
-// between `splits` work-groups per (row, KV head)): each wave streams its
-// own contiguous run of kpw keys in 32-key blocks and waits on no other wave
-// until the final merge.  Work-group = (split, KV head, row); the G query
+// The K rows of keys [k0, k1) (at most 32) as A operand rows: key 16 t + l %
+// 16, dims 32 st + 8 (l / 16) .. + 8; keys past the end repeat the last.
+template <int HD>
+__device__ __forceinline__ void load_k_block(const bf16_t* __restrict__ k, int k0, int k1, uint4 (&kr)[2][HD / 32]) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    const bf16_t* src = k + (int64_t)min(k0 + 16 * t + (lane & 15), k1 - 1) * HD + 8 * (lane >> 4);
+#pragma unroll
+    for (int st = 0; st < HD / 32; ++st) kr[t][st] = *reinterpret_cast<const uint4*>(src + 32 * st);
+  }
+}
+
+// The V rows of the same keys into an LDS buffer of 32 rows, chunks swizzled
+// (vslot).  Buffer loads: with global_load_lds in flight (an access of two
+// address spaces to the compiler) every use of a loaded register would wait
+// for all loads (vmcnt 0), the next block's among them.
+template <int HD>
+__device__ __forceinline__ void copy_v_block(BufRsrc v, int k0, int k1, bf16_t* dst) {
+  constexpr int CPK = HD / 8, KPD = 64 / CPK;   // chunks per key, keys per copy
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int i = 0; i < 32 / KPD; ++i) {
+    const int kk = i * KPD + lane / CPK;
+    const int j = min(kk, k1 - k0 - 1);
+    dma16(v, (uint32_t)((j * HD + 8 * vslot<CPK>(kk, lane % CPK)) * 2), k0 * HD * 2, dst + i * 512);
+  }
+}
+
+// Decode attention over the prefix (unless another pass attends it) and the
+// tail for bf16, head_dim 64 or 128, on MFMA, with the keys split between the
+// NW waves of a work-group (and between `splits` work-groups per (row, KV
+// head)): each wave streams its own contiguous run of bpw 32-key blocks and
+// waits on no other wave until the final merge.  Work-group = (split, KV head, row); the G query
 // heads of the KV head are the MFMA's 16 columns (columns >= G are zero
 // queries whose results are dropped).
 //   S^T = K Q^T: the A operand (16 keys x 32 dims) is loaded from memory
@@ -333,7 +362,7 @@ __device__ __forceinline__ int vslot(int k, int c) {
 template <int HD, int G, int NW>
 __global__ void __launch_bounds__(64 * NW)
 decode_wave_kernel(const float* __restrict__ q, const bf16_t* __restrict__ kpre, const bf16_t* __restrict__ vpre,
-                   int P, bf16_t* ktail, bf16_t* vtail, int cap, int lt, int hq, int hkv, int kpw, int key0,
+                   int P, bf16_t* ktail, bf16_t* vtail, int cap, int lt, int hq, int hkv, int bpw, int prefix,
                    int splits, float* __restrict__ part, bf16_t* __restrict__ out, float qscale,
                    const float* __restrict__ qpart, int qsplits, int qkv_dim, const float2* __restrict__ rope,
                    float* __restrict__ qout) {
@@ -342,7 +371,6 @@ decode_wave_kernel(const float* __restrict__ q, const bf16_t* __restrict__ kpre,
   constexpr int CPK = HD / 8;           // 16-byte chunks per key row
   constexpr int VB = 32 * HD;           // bf16 elements of a 32-key V block
   constexpr int NDMA = VB * 2 / 1024;   // 1 KB copies per V block
-  constexpr int KPD = 64 / CPK;         // keys per copy
   constexpr int INFLIGHT = 2 * KS + NDMA;  // memory operations of one block
   static_assert(HD == 64 || HD == 128, "head_dim");
   static_assert(G >= 1 && G <= 16, "query heads per KV head");
@@ -351,40 +379,29 @@ decode_wave_kernel(const float* __restrict__ q, const bf16_t* __restrict__ kpre,
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int fr = lane & 15, fg = lane >> 4;
-  const int total = P + lt;
-  const int w0 = key0 + (split * NW + wave) * kpw;
-  const int w1 = min(total, w0 + kpw);
-  const int nb = w0 < w1 ? (w1 - w0 + 31) >> 5 : 0;
+  // The keys in 32-key blocks: nbp of the prefix (none when another pass
+  // attends it), then the tail's; this wave's are blocks [i0, i1).
+  const int nbp = prefix ? (P + 31) >> 5 : 0, nball = nbp + ((lt + 31) >> 5);
+  const int i0 = min(nball, (split * NW + wave) * bpw), i1 = min(nball, i0 + bpw);
+  const int nb = i1 - i0;
   const bf16_t* kt = ktail + ((int64_t)row * hkv + h) * cap * HD;
   const bf16_t* vt = vtail + ((int64_t)row * hkv + h) * cap * HD;
   const bf16_t* kp = kpre + (int64_t)h * P * HD;
   const bf16_t* vp = vpre + (int64_t)h * P * HD;
+  const BufRsrc rvp = buf_rsrc(vp), rvt = buf_rsrc(vt);
   bf16_t* vbuf = lds + wave * 2 * VB;
 
-  auto load_k = [&](int b, uint4 (&kr)[2][KS]) {
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      const int j = min(w0 + 32 * b + 16 * t + fr, w1 - 1);
-      const bf16_t* src = j < P ? kp + (int64_t)j * HD : kt + (int64_t)(j - P) * HD;
-#pragma unroll
-      for (int st = 0; st < KS; ++st) kr[t][st] = *reinterpret_cast<const uint4*>(src + 32 * st + 8 * fg);
-    }
-  };
+  auto in_tail = [&](int b) { return i0 + b >= nbp; };
+  auto key0 = [&](int b) { return 32 * (i0 + b - (in_tail(b) ? nbp : 0)); };
+  auto keyend = [&](int b) { return min(key0(b) + 32, in_tail(b) ? lt : P); };
+  auto load_k = [&](int b, uint4 (&kr)[2][KS]) { load_k_block<HD>(in_tail(b) ? kt : kp, key0(b), keyend(b), kr); };
   auto copy_v = [&](int b, int buf) {
-    bf16_t* dst = vbuf + buf * VB;
-#pragma unroll
-    for (int i = 0; i < NDMA; ++i) {
-      const int kk = i * KPD + lane / CPK;
-      const int c = vslot<CPK>(kk, lane % CPK);
-      const int j = min(w0 + 32 * b + kk, w1 - 1);
-      const bf16_t* src = (j < P ? vp + (int64_t)j * HD : vt + (int64_t)(j - P) * HD) + 8 * c;
-      dma16(reinterpret_cast<const char*>(src), dst + i * 512);
-    }
+    copy_v_block<HD>(in_tail(b) ? rvt : rvp, key0(b), keyend(b), vbuf + buf * VB);
   };
 
   // The first block's loads go out before anything else unless it holds
   // the newest key, which this wave writes first (fused QKV finalize).
-  const bool writer = qpart && nb > 0 && w1 == total;
+  const bool writer = qpart && nb > 0 && i1 == nball;
   const bool early = nb > 0 && !(writer && nb == 1);
   uint4 ka[2][KS], kb[2][KS];
   if (early) {
@@ -477,8 +494,15 @@ decode_wave_kernel(const float* __restrict__ q, const bf16_t* __restrict__ kpre,
   float m = -INFINITY, l = 0.f;
   // transpose-read addresses: lane names 4 dims (dt 16 + 4 (fr & 3) ..) of
   // key 4 fg + (fr >> 2), and of the key 16 on
-  const int kr0 = 4 * fg + (fr >> 2), kr1 = kr0 + 16;
-  auto compute = [&](int b, const uint4 (&kr)[2][KS], int buf) {
+  // (in the first buffer; the second key's row sits 16 rows on, same slots)
+  uint32_t vaddr[DT];
+  {
+    const int kr0 = 4 * fg + (fr >> 2);
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+      vaddr[dt] = lds_addr(vbuf + kr0 * HD + 8 * vslot<CPK>(kr0, 2 * dt + ((fr & 3) >> 1)) + 4 * (fr & 1));
+  }
+  auto compute = [&](int b, const uint4 (&kr)[2][KS], auto bufc) {
     f32x4 st[2];
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
@@ -488,12 +512,12 @@ decode_wave_kernel(const float* __restrict__ q, const bf16_t* __restrict__ kpre,
         st[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kr[t][s2]), qf[s2], st[t], 0, 0,
                                                         0);
     }
-    const int jb = w0 + 32 * b + 4 * fg;
+    const int left = keyend(b) - key0(b) - 4 * fg;   // keys of the block from this lane's first
     float sv[8];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      sv[i] = jb + i < w1 ? st[0][i] : -INFINITY;
-      sv[4 + i] = jb + 16 + i < w1 ? st[1][i] : -INFINITY;
+      sv[i] = i < left ? st[0][i] : -INFINITY;
+      sv[4 + i] = 16 + i < left ? st[1][i] : -INFINITY;
     }
     float mt = sv[0];
 #pragma unroll
@@ -513,43 +537,54 @@ decode_wave_kernel(const float* __restrict__ q, const bf16_t* __restrict__ kpre,
     }
     l = l * corr + ps;
     m = mn;
-    const bf16_t* vs = vbuf + buf * VB;
+    constexpr int BUF = decltype(bufc)::value;
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt) {
-      const int c = 2 * dt + ((fr & 3) >> 1), e4 = 4 * (fr & 1);
-      const i16x4 lo = lds_read_tr16(vs + kr0 * HD + 8 * vslot<CPK>(kr0, c) + e4);
-      const i16x4 hi = lds_read_tr16(vs + kr1 * HD + 8 * vslot<CPK>(kr1, c) + e4);
-      o[dt] *= corr;
-      o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tr16_pair(lo, hi), pf, o[dt], 0, 0, 0);
+    for (int d0 = 0; d0 < DT; d0 += 4) {
+      const uint32_t va[4] = {vaddr[d0], vaddr[d0 + 1], vaddr[d0 + 2], vaddr[d0 + 3]};
+      i16x4 lo[4], hi[4];
+      lds_read_tr16_pairs<4, BUF * VB * 2, (BUF * VB + 16 * HD) * 2>(va, lo, hi);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        o[d0 + i] *= corr;
+        o[d0 + i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tr16_pair(lo[i], hi[i]), pf, o[d0 + i], 0, 0, 0);
+      }
     }
   };
 
+  // One block ahead: a block's loads are in flight while the one before is
+  // computed.  Every fetch in the loop is unconditional, so the compiler's
+  // own waits for the K registers count the younger block's loads as in
+  // flight instead of draining them.
+  const std::integral_constant<int, 0> buf0{};
+  const std::integral_constant<int, 1> buf1{};
+  auto compute_after = [&](auto left, int b, const uint4 (&kr)[2][KS], auto bufc) {
+    __builtin_amdgcn_sched_barrier(0);   // (the fetch before it stays before it)
+    vm_wait<decltype(left)::value>();
+    compute(b, kr, bufc);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  const std::integral_constant<int, INFLIGHT> next{};
   if (nb > 0) {
     if (!early) {
       load_k(0, ka);
       copy_v(0, 0);
     }
-    for (int b = 0; b < nb; b += 2) {
-      if (b + 1 < nb) {
-        load_k(b + 1, kb);
-        copy_v(b + 1, 1);
-        vm_wait<INFLIGHT>();
-      } else {
-        vm_wait<0>();
-      }
-      compute(b, ka, 0);
-      if (b + 1 < nb) {
-        asm volatile("" ::: "memory");
-        if (b + 2 < nb) {
-          load_k(b + 2, ka);
-          copy_v(b + 2, 0);
-          vm_wait<INFLIGHT>();
-        } else {
-          vm_wait<0>();
-        }
-        compute(b + 1, kb, 1);
-        asm volatile("" ::: "memory");
-      }
+    int b = 0;
+    for (; b + 2 < nb; b += 2) {
+      load_k(b + 1, kb);
+      copy_v(b + 1, 1);
+      compute_after(next, b, ka, buf0);
+      load_k(b + 2, ka);
+      copy_v(b + 2, 0);
+      compute_after(next, b + 1, kb, buf1);
+    }
+    if (b + 1 < nb) {
+      load_k(b + 1, kb);
+      copy_v(b + 1, 1);
+      compute_after(next, b, ka, buf0);
+      compute_after(buf0, b + 1, kb, buf1);
+    } else {
+      compute_after(buf0, b, ka, buf0);
     }
   }
 
@@ -623,7 +658,6 @@ decode_group_kernel(const float* __restrict__ q, const bf16_t* __restrict__ kpre
   constexpr int KS = HD / 32, DT = HD / 16, CPK = HD / 8;
   constexpr int VB = 32 * HD;
   constexpr int NDMA = VB * 2 / 1024;
-  constexpr int KPD = 64 / CPK;
   constexpr int INFLIGHT = 2 * KS + NDMA;
   static_assert(HD == 64 || HD == 128, "head_dim");
   static_assert(G == 2 || G == 4 || G == 8, "query heads per KV head");
@@ -646,6 +680,7 @@ decode_group_kernel(const float* __restrict__ q, const bf16_t* __restrict__ kpre
   const bf16_t* vt = vtail + ((int64_t)(rowvalid ? row : 0) * hkv + h) * cap * HD;
   const bf16_t* kp = kpre + (int64_t)h * P * HD;
   const bf16_t* vp = vpre + (int64_t)h * P * HD;
+  const BufRsrc rvp = buf_rsrc(vp), rvt = buf_rsrc(vt);
   bf16_t* vbuf = lds + wave * 2 * VB;
 
   // fused QKV finalize: the newest key's K (rotated) and V row of this row
@@ -722,27 +757,15 @@ decode_group_kernel(const float* __restrict__ q, const bf16_t* __restrict__ kpre
       for (int e = 0; e < 8; ++e) qf[st][e] = (__bf16)(qvalid ? x[st][e] * qscale : 0.f);
   }
 
-  // block b of a run: keys [b0 + 32 b, min(b0 + 32 b + 32, b1)) of (kb, vb)
-  auto load_k = [&](const bf16_t* kb_, int k0, int k1, uint4 (&kr)[2][KS]) {
+  // transpose-read addresses: lane names 4 dims (dt 16 + 4 (fr & 3) ..) of key
+  // 4 fg + (fr >> 2) in the first buffer; the key 16 on has the same slots
+  uint32_t vaddr[DT];
+  {
+    const int kr0 = 4 * fg + (fr >> 2);
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      const int j = min(k0 + 16 * t + fr, k1 - 1);
-      const bf16_t* src = kb_ + (int64_t)j * HD;
-#pragma unroll
-      for (int st = 0; st < KS; ++st) kr[t][st] = *reinterpret_cast<const uint4*>(src + 32 * st + 8 * fg);
-    }
-  };
-  auto copy_v = [&](const bf16_t* vb_, int k0, int k1, int buf) {
-    bf16_t* dst = vbuf + buf * VB;
-#pragma unroll
-    for (int i = 0; i < NDMA; ++i) {
-      const int kk = i * KPD + lane / CPK;
-      const int c = vslot<CPK>(kk, lane % CPK);
-      const int j = min(k0 + kk, k1 - 1);
-      dma16(reinterpret_cast<const char*>(vb_ + (int64_t)j * HD + 8 * c), dst + i * 512);
-    }
-  };
-  const int kr0 = 4 * fg + (fr >> 2), kr1 = kr0 + 16;
+    for (int dt = 0; dt < DT; ++dt)
+      vaddr[dt] = lds_addr(vbuf + kr0 * HD + 8 * vslot<CPK>(kr0, 2 * dt + ((fr & 3) >> 1)) + 4 * (fr & 1));
+  }
   f32x4 o[DT];
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -750,7 +773,7 @@ decode_group_kernel(const float* __restrict__ q, const bf16_t* __restrict__ kpre
   // A block of a row's tail serves only that row's G columns: the other
   // columns' scores are masked, so prefix and tail blocks share one
   // softmax state per column.
-  auto compute = [&](int k0, int k1, bool tail, const uint4 (&kr)[2][KS], int buf) {
+  auto compute = [&](int k0, int k1, bool tail, const uint4 (&kr)[2][KS], auto bufc) {
     f32x4 st[2];
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
@@ -786,14 +809,17 @@ decode_group_kernel(const float* __restrict__ q, const bf16_t* __restrict__ kpre
     }
     l = l * corr + ps;
     m = mn;
-    const bf16_t* vs = vbuf + buf * VB;
+    constexpr int BUF = decltype(bufc)::value;
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt) {
-      const int c = 2 * dt + ((fr & 3) >> 1), e4 = 4 * (fr & 1);
-      const i16x4 lo = lds_read_tr16(vs + kr0 * HD + 8 * vslot<CPK>(kr0, c) + e4);
-      const i16x4 hi = lds_read_tr16(vs + kr1 * HD + 8 * vslot<CPK>(kr1, c) + e4);
-      o[dt] *= corr;
-      o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tr16_pair(lo, hi), pf, o[dt], 0, 0, 0);
+    for (int d0 = 0; d0 < DT; d0 += 4) {
+      const uint32_t va[4] = {vaddr[d0], vaddr[d0 + 1], vaddr[d0 + 2], vaddr[d0 + 3]};
+      i16x4 lo[4], hi[4];
+      lds_read_tr16_pairs<4, BUF * VB * 2, (BUF * VB + 16 * HD) * 2>(va, lo, hi);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        o[d0 + i] *= corr;
+        o[d0 + i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tr16_pair(lo[i], hi[i]), pf, o[d0 + i], 0, 0, 0);
+      }
     }
   };
   // The wave's blocks: its prefix share [pk0, pk1) of (kp, vp), then its
@@ -807,31 +833,35 @@ decode_group_kernel(const float* __restrict__ q, const bf16_t* __restrict__ kpre
   auto keyend = [&](int b) { return b < np ? min(pk0 + 32 * b + 32, pk1) : min(tk0 + 32 * (b - np) + 32, tk1); };
   auto fetch = [&](int b, uint4 (&kr)[2][KS], int buf) {
     const bool tail = b >= np;
-    load_k(tail ? kt : kp, key0(b), keyend(b), kr);
-    copy_v(tail ? vt : vp, key0(b), keyend(b), buf);
+    load_k_block<HD>(tail ? kt : kp, key0(b), keyend(b), kr);
+    copy_v_block<HD>(tail ? rvt : rvp, key0(b), keyend(b), vbuf + buf * VB);
+  };
+  // (fetches in the loop unconditional, as in decode_wave_kernel)
+  const std::integral_constant<int, 0> buf0{};
+  const std::integral_constant<int, 1> buf1{};
+  const std::integral_constant<int, INFLIGHT> next{};
+  auto compute_after = [&](auto left, int b, const uint4 (&kr)[2][KS], auto bufc) {
+    __builtin_amdgcn_sched_barrier(0);
+    vm_wait<decltype(left)::value>();
+    compute(key0(b), keyend(b), b >= np, kr, bufc);
+    __builtin_amdgcn_sched_barrier(0);
   };
   if (nb > 0) {
     uint4 ka[2][KS], kb[2][KS];
     fetch(0, ka, 0);
-    for (int b = 0; b < nb; b += 2) {
-      if (b + 1 < nb) {
-        fetch(b + 1, kb, 1);
-        vm_wait<INFLIGHT>();
-      } else {
-        vm_wait<0>();
-      }
-      compute(key0(b), keyend(b), b >= np, ka, 0);
-      if (b + 1 < nb) {
-        asm volatile("" ::: "memory");
-        if (b + 2 < nb) {
-          fetch(b + 2, ka, 0);
-          vm_wait<INFLIGHT>();
-        } else {
-          vm_wait<0>();
-        }
-        compute(key0(b + 1), keyend(b + 1), b + 1 >= np, kb, 1);
-        asm volatile("" ::: "memory");
-      }
+    int b = 0;
+    for (; b + 2 < nb; b += 2) {
+      fetch(b + 1, kb, 1);
+      compute_after(next, b, ka, buf0);
+      fetch(b + 2, ka, 0);
+      compute_after(next, b + 1, kb, buf1);
+    }
+    if (b + 1 < nb) {
+      fetch(b + 1, kb, 1);
+      compute_after(next, b, ka, buf0);
+      compute_after(buf0, b + 1, kb, buf1);
+    } else {
+      compute_after(buf0, b, ka, buf0);
     }
   }
 
@@ -1106,27 +1136,27 @@ int decode_attn_splits(int rows, int hkv, int keys) {
   return std::max(old_form, wave_form_max);
 }
 
-// Work split of decode_wave_kernel over `keys` keys of rows x hkv (row, KV
-// head) pairs: about kWaveTarget waves in all (one round of resident waves:
-// LDS holds ten per CU at head_dim 128), each with at least two 32-key
-// blocks; NW waves per work-group (1, 2, 4 or 8) and `splits` work-groups
-// per pair, each wave kpw keys (a multiple of 32).  Where eight waves per
-// pair already give a thousand waves, one work-group of eight takes the pair
-// (no split partials, no merge launch).
+// Work split of decode_wave_kernel over the 32-key blocks of a prefix of P
+// and a tail of lt keys, for rows x hkv (row, KV head) pairs: about
+// kWaveTarget waves in all (one round of resident waves: LDS holds ten per CU
+// at head_dim 128), each with at least two blocks; NW waves per work-group (1,
+// 2, 4 or 8) and `splits` work-groups per pair, each wave bpw blocks.  Where
+// eight waves per pair already give a thousand waves, one work-group of eight
+// takes the pair (no split partials, no merge launch).
 struct WavePlan {
-  int nw, splits, kpw;
+  int nw, splits, bpw;
 };
-static WavePlan wave_plan(int rows, int hkv, int keys) {
+static WavePlan wave_plan(int rows, int hkv, int P, int lt) {
   const int64_t pairs = std::max<int64_t>(1, (int64_t)rows * hkv);
-  const int blocks = std::max(1, (keys + 31) / 32);
+  const int blocks = std::max(1, (P + 31) / 32 + (lt + 31) / 32);
   int want = (int)std::max<int64_t>(1, kWaveTarget / pairs);
   want = std::max(1, std::min(want, blocks / 2));
   if (want > 8 && pairs * 8 >= 1024) want = 8;
   WavePlan w;
   w.nw = want >= 8 ? 8 : (want >= 4 ? 4 : (want >= 2 ? 2 : 1));
   const int per = (want + w.nw - 1) / w.nw * w.nw;    // waves per pair
-  w.kpw = 32 * ((blocks + per - 1) / per);
-  w.splits = std::max(1, (keys + w.nw * w.kpw - 1) / (w.nw * w.kpw));
+  w.bpw = (blocks + per - 1) / per;
+  w.splits = std::max(1, (blocks + w.nw * w.bpw - 1) / (w.nw * w.bpw));
   return w;
 }
 
@@ -1172,12 +1202,12 @@ static void launch_group(const DecodeAttnArgs& a, float qscale, hipStream_t s) {
 }
 
 template <int HD, int G>
-static void launch_wave(const DecodeAttnArgs& a, int key0, const WavePlan& w, bool direct, float qscale,
+static void launch_wave(const DecodeAttnArgs& a, bool prefix, const WavePlan& w, bool direct, float qscale,
                         hipStream_t s) {
 #define SR_WAVE(NW)                                                                                              \
   SR_LAUNCH((decode_wave_kernel<HD, G, NW>), dim3(w.splits, a.hkv, a.rows), dim3(64 * NW), 0, s, a.q,  \
                      (const bf16_t*)a.kpre, (const bf16_t*)a.vpre, a.P, (bf16_t*)a.ktail, (bf16_t*)a.vtail,       \
-                     a.cap, a.lt, a.hq, a.hkv, w.kpw, key0, w.splits, a.part, direct ? (bf16_t*)a.out : nullptr, \
+                     a.cap, a.lt, a.hq, a.hkv, w.bpw, (int)prefix, w.splits, a.part, direct ? (bf16_t*)a.out : nullptr, \
                      qscale, a.qpart, a.qsplits, a.qkv_dim, a.rope, a.qout)
   if (w.nw == 8) SR_WAVE(8);
   else if (w.nw == 4) SR_WAVE(4);
@@ -1213,17 +1243,16 @@ static void launch_decode(const DecodeAttnArgs& a, hipStream_t s) {
       const bool pre = prefix_by_mfma(a.dtype, HD, a.P, a.rows);
       SR_REQUIRE(!a.qpart || (a.lt >= 1 && a.rope && a.qsplits >= 1), SR_ERR_INTERNAL,
                  "fused QKV finalize needs a new key");
-      const int key0 = pre ? a.P : 0;
-      const int keys = a.P + a.lt - key0;
-      if (keys > 0) {
-        const WavePlan w = wave_plan(a.rows, a.hkv, keys);
+      const int pkeys = pre ? 0 : a.P;
+      if (pkeys + a.lt > 0) {
+        const WavePlan w = wave_plan(a.rows, a.hkv, pkeys, a.lt);
         const bool direct = !pre && w.splits == 1;
         if (!direct)
           SR_REQUIRE((size_t)a.rows * a.hq * w.splits * (HD + 2) <= a.part_cap, 5,
                      "attention partial buffer too small");
         DecodeAttnArgs b = a;
         if (!pre) b.qout = nullptr;  // only the prefix pass reads q back
-        launch_wave<HD, G>(b, key0, w, direct, qscale, s);
+        launch_wave<HD, G>(b, !pre, w, direct, qscale, s);
         if (pre) {
           prefix_pass(w.splits);
         } else if (!direct) {
@@ -1316,9 +1345,9 @@ size_t decode_attn_part_floats(const DecodeAttnArgs& a) {
   if (group_form(a.dtype, a.hd, g, a.P, a.rows)) return 0;
   if (wave_form(a.dtype, a.hd, g)) {
     const bool pre = prefix_by_mfma(a.dtype, a.hd, a.P, a.rows);
-    const int keys = a.P + a.lt - (pre ? a.P : 0);
-    if (keys <= 0) return 0;
-    const WavePlan w = wave_plan(a.rows, a.hkv, keys);
+    const int pkeys = pre ? 0 : a.P;
+    if (pkeys + a.lt <= 0) return 0;
+    const WavePlan w = wave_plan(a.rows, a.hkv, pkeys, a.lt);
     return (!pre && w.splits == 1) ? 0 : per * w.splits;
   }
   if (prefix_by_mfma(a.dtype, a.hd, a.P, a.rows)) {

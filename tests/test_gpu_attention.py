@@ -54,6 +54,15 @@ CASES = [
     ("bf16", 64, 8, 2, 64, 128, 33, 40),
     ("bf16", 128, 64, 8, 101, 256, 77, 80),
     ("bf16", 128, 32, 8, 64, 33, 1, 8),
+    # one, two and three blocks a wave; a partial prefix block before the tail;
+    # one block in all; tails of whole blocks
+    ("bf16", 128, 32, 8, 3, 33, 64, 64),
+    ("bf16", 64, 32, 8, 2, 1, 31, 32),
+    ("bf16", 64, 8, 8, 5, 95, 97, 100),
+    ("bf16", 128, 8, 8, 7, 0, 31, 31),
+    ("bf16", 128, 32, 8, 64, 65, 32, 33),
+    ("bf16", 128, 64, 8, 70, 31, 161, 161),
+    ("bf16", 64, 16, 8, 90, 200, 64, 64),
     ("f32", 32, 4, 4, 16, 32, 17, 64),
     ("f32", 32, 8, 1, 6, 5, 3, 3),
 ]
