@@ -31,6 +31,10 @@ namespace sr {
 
 constexpr float kLog2e = 1.4426950408889634f;
 
+// Online softmax: log2 of the growth of the scores that moves the reference
+// maximum of a column.
+constexpr float kLazyMax = 8.0f;
+
 __device__ __forceinline__ float exp2_or_zero(float x) { return x == -INFINITY ? 0.f : exp2f(x); }
 
 // Work-group barrier after this wave's LDS reads and writes complete; vector
@@ -524,19 +528,26 @@ decode_wave_kernel(const float* __restrict__ q, const bf16_t* __restrict__ kpre,
     for (int i = 1; i < 8; ++i) mt = fmaxf(mt, sv[i]);
     mt = fmaxf(mt, __shfl_xor(mt, 16, 64));
     mt = fmaxf(mt, __shfl_xor(mt, 32, 64));
-    const float mn = fmaxf(m, mt);
-    const bool none = mn == -INFINITY;
-    const float corr = none ? 1.f : exp2f(m - mn);
+    // the reference maximum moves (and the accumulators are rescaled) only
+    // when some column exceeds it by 2^8
+    if (__any(mt > m + kLazyMax)) {
+      const float mn = fmaxf(m, mt);
+      const float corr = mn == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m - mn);
+      l *= corr;
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) o[dt] *= corr;
+      m = mn;
+    }
+    const float mr = m == -INFINITY ? 0.f : m;   // (a column without a key so far)
     bf16x8 pf;
     float ps = 0.f;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      const float pv = none ? 0.f : exp2f(sv[i] - mn);
+      const float pv = __builtin_amdgcn_exp2f(sv[i] - mr);
       ps += pv;
       pf[i] = (__bf16)pv;
     }
-    l = l * corr + ps;
-    m = mn;
+    l += ps;
     constexpr int BUF = decltype(bufc)::value;
 #pragma unroll
     for (int d0 = 0; d0 < DT; d0 += 4) {
@@ -545,7 +556,6 @@ decode_wave_kernel(const float* __restrict__ q, const bf16_t* __restrict__ kpre,
       lds_read_tr16_pairs<4, BUF * VB * 2, (BUF * VB + 16 * HD) * 2>(va, lo, hi);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        o[d0 + i] *= corr;
         o[d0 + i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tr16_pair(lo[i], hi[i]), pf, o[d0 + i], 0, 0, 0);
       }
     }
@@ -796,19 +806,26 @@ decode_group_kernel(const float* __restrict__ q, const bf16_t* __restrict__ kpre
     for (int i = 1; i < 8; ++i) mt = fmaxf(mt, sv[i]);
     mt = fmaxf(mt, __shfl_xor(mt, 16, 64));
     mt = fmaxf(mt, __shfl_xor(mt, 32, 64));
-    const float mn = fmaxf(m, mt);
-    const bool none = mn == -INFINITY;
-    const float corr = none ? 1.f : exp2f(m - mn);
+    // the reference maximum moves (and the accumulators are rescaled) only
+    // when some column exceeds it by 2^8
+    if (__any(mt > m + kLazyMax)) {
+      const float mn = fmaxf(m, mt);
+      const float corr = mn == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m - mn);
+      l *= corr;
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) o[dt] *= corr;
+      m = mn;
+    }
+    const float mr = m == -INFINITY ? 0.f : m;   // (a column without a key so far)
     bf16x8 pf;
     float ps = 0.f;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      const float pv = none ? 0.f : exp2f(sv[i] - mn);
+      const float pv = __builtin_amdgcn_exp2f(sv[i] - mr);
       ps += pv;
       pf[i] = (__bf16)pv;
     }
-    l = l * corr + ps;
-    m = mn;
+    l += ps;
     constexpr int BUF = decltype(bufc)::value;
 #pragma unroll
     for (int d0 = 0; d0 < DT; d0 += 4) {
@@ -817,7 +834,6 @@ decode_group_kernel(const float* __restrict__ q, const bf16_t* __restrict__ kpre
       lds_read_tr16_pairs<4, BUF * VB * 2, (BUF * VB + 16 * HD) * 2>(va, lo, hi);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        o[d0 + i] *= corr;
         o[d0 + i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tr16_pair(lo[i], hi[i]), pf, o[d0 + i], 0, 0, 0);
       }
     }
@@ -1510,7 +1526,6 @@ prefill_attn_kernel(const float* __restrict__ q, const T* __restrict__ kpre, con
 // (16 exponentials of 32 keys take as long as half their MFMAs), MFMA and LDS
 // waits overlap only across the two waves of a SIMD.
 constexpr int PF_NST = 4;            // stages
-constexpr float PF_LAZY = 8.0f;      // log2 of the growth that moves the maximum
 
 template <int HD, int G, int QB, int KT>
 __global__ void __launch_bounds__(64 * G * QB, 2)
@@ -1667,7 +1682,7 @@ prefill_attn_mfma_kernel(const float* __restrict__ q, const bf16_t* __restrict__
 #pragma unroll
     for (int e = 1; e < 16; ++e) mt = fmaxf(mt, sc[e]);
     mt = fmaxf(mt, other_half(mt));
-    if (__any(mt > m + PF_LAZY)) {
+    if (__any(mt > m + kLazyMax)) {
       const float mn = fmaxf(m, mt);
       const float corr = mn == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m - mn);
       l *= corr;
