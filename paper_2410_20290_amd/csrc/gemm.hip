@@ -516,13 +516,14 @@ gemm_dma_kernel(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict_
                 float* __restrict__ partial) {
   constexpr int BM = 256, BNL = 256, BK = 64;
   constexpr int BN_OUT = PAIRED ? 128 : 256;
-  constexpr int STAGE = (BM + BNL) * BK;  // bf16 elements per stage
-  constexpr int HALF = BM * BK;           // bf16 elements of the A (or B) rows of a stage
+  constexpr int HALF = BM * BK;           // bf16 elements of the A (or B) rows of a K step
+  static_assert(BM == BNL, "A and B rows share the slots");
   static_assert(BRING == 2 || BRING == 3, "weight ring depth");
-  __shared__ __attribute__((aligned(1024))) bf16_t lds[BRING == 2 ? 2 * STAGE : 2 * HALF + 3 * HALF];
-  // A rows of ring slot `a`, B rows of ring slot `b`
-  auto a_base = [&](int a) { return lds + (BRING == 2 ? a * STAGE : a * HALF); };
-  auto b_base = [&](int b) { return lds + (BRING == 2 ? b * STAGE + HALF : 2 * HALF + b * HALF); };
+  __shared__ __attribute__((aligned(1024))) bf16_t lds[5 * HALF];
+  // BRING 3: A rows of ring slot `a`, B rows of ring slot `b`; BRING 2: five
+  // slots for A and B rows alike
+  auto a_base = [&](int a) { return lds + a * HALF; };
+  auto b_base = [&](int b) { return lds + (BRING == 2 ? b * HALF : 2 * HALF + b * HALF); };
 
   const TileIdx tile = tile_of((M + BM - 1) / BM, (N + BN_OUT - 1) / BN_OUT, K / k_per_split);
   if (!tile.valid) return;
@@ -617,19 +618,88 @@ gemm_dma_kernel(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict_
   // Every step issues the DMAs of the step after next; past the last step
   // the source is clamped to the last step (data never read), which keeps
   // every wait below the same at each step.
-  issue_half(0, 0, 0);
-  issue_half(0, 0, 1);
-  issue_half(min(1, nk - 1), 1, 0);
-  issue_half(min(1, nk - 1), 1, 1);
   if constexpr (BRING == 3) {
+    issue_half(0, 0, 0);
+    issue_half(0, 0, 1);
+    issue_half(min(1, nk - 1), 1, 0);
+    issue_half(min(1, nk - 1), 1, 1);
     issue_half(min(2, nk - 1), 2, 1);
     SR_VM_BARRIER(24);
   } else {
+    issue_half(0, 0, 0);
+    issue_half(0, 1, 1);
+    issue_half(min(1, nk - 1), 2, 0);
+    issue_half(min(1, nk - 1), 3, 1);
     SR_VM_BARRIER(16);
   }
   __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): no scalar loads in flight past here
   bf16x8 a0[4], b0[4], a1[4], b1[4], a2[4], b2[4];
-  read_frags(0, 0, 0, a0, b0);
+  read_frags(0, BRING == 3 ? 0 : 1, 0, a0, b0);
+  auto mfma2 = [&](int p, const bf16x8(&af)[4], const bf16x8(&bfr)[4]) {
+    const int i = p >> 1, j = (p & 1) * 2;
+    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[j], af[i], acc[i][j], 0, 0, 0);
+    acc[i][j + 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[j + 1], af[i], acc[i][j + 1], 0, 0, 0);
+  };
+  // BRING 2.  The rows of A and of B of the steps take turns in five slots of
+  // 32 KB (A_t in slot 2 t mod 5, B_t in the one after), so the copies spread
+  // over the whole step: the slot of B_(t-1) is free from the start of step t
+  // and takes A_(t+2) under quarters 0 and 1; the barrier after quarter 1
+  // frees the slots of step t and B_(t+2) goes to that of A_t under quarters
+  // 2 and 3.  One copy per four MFMAs; with two stages of both they all had to
+  // go out under two quarters, which filled the copy path and held up the
+  // MFMA issue behind it.  sa: slot of A_t.
+  auto step5 = [&](int t, int sa, bf16x8(&xa)[4], bf16x8(&xb)[4], bf16x8(&ya)[4], bf16x8(&yb)[4], bf16x8(&za)[4],
+                   bf16x8(&zb)[4]) {
+    auto slot = [&](int k) { return sa + k >= 5 ? sa + k - 5 : sa + k; };
+    const int koff = min(t + 2, nk - 1) * BK * 2;
+    const bf16_t* ar = a_base(sa) + wm0 * BK;
+    const bf16_t* br = b_base(slot(1)) + wn0 * BK;
+    const bf16_t* an = a_base(slot(2)) + wm0 * BK + foff[0];
+    const bf16_t* bn = b_base(slot(3)) + wn0 * BK + foff[0];
+    bf16_t* ad = a_base(slot(4)) + wave * 512;
+    bf16_t* bd = b_base(sa) + wave * 512;
+    auto frag = [](const bf16_t* p, int i) { return *reinterpret_cast<const bf16x8*>(p + 32 * i * BK); };
+#pragma unroll
+    for (int p = 0; p < 8; ++p) {
+      mfma2(p, xa, xb);
+      if (p < 4) {
+        ya[p] = frag(ar + foff[1], p);
+        yb[p] = frag(br + foff[1], p);
+      } else {
+        za[p - 4] = frag(ar + foff[2], p - 4);
+        zb[p - 4] = frag(br + foff[2], p - 4);
+      }
+      if (p & 1) dma16(ra, aoff[p >> 1], koff, ad + 2048 * (p >> 1));
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int p = 0; p < 8; ++p) {
+      mfma2(p, ya, yb);
+      if (p < 4) xa[p] = frag(ar + foff[3], p);
+      else xb[p - 4] = frag(br + foff[3], p - 4);
+      if (p & 1) dma16(ra, aoff[4 + (p >> 1)], koff, ad + 2048 * (4 + (p >> 1)));
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    // step t has been read by all waves; step t + 1 landed (all but this
+    // wave's newest copies, the A rows of step t + 2)
+    SR_VM_BARRIER(8);
+    __builtin_amdgcn_sched_barrier(0);
+    // (after the last step the next quarter 0 is a stale buffer, never used)
+#pragma unroll
+    for (int p = 0; p < 8; ++p) {
+      mfma2(p, za, zb);
+      if (p < 4) ya[p] = frag(an, p);
+      else yb[p - 4] = frag(bn, p - 4);
+      if (p & 1) dma16(rb, boff[p >> 1], koff, bd + 2048 * (p >> 1));
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int p = 0; p < 8; ++p) {
+      mfma2(p, xa, xb);
+      if (p & 1) dma16(rb, boff[4 + (p >> 1)], koff, bd + 2048 * (4 + (p >> 1)));
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
   // One K step with its quarter 0 in (xa, xb); quarter 3 reuses those
   // registers and the next step's quarter 0 goes to (ya, yb).  bb, bbn: B
   // ring slots of steps t and t + 1.  One barrier per step, after quarter 1:
@@ -648,8 +718,7 @@ gemm_dma_kernel(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict_
     read_frags(buf, bb, 3, xa, xb);
     mfma(ya, yb);
     reads8();
-    if constexpr (BRING == 3) SR_VM_BARRIER(8);
-    else SR_VM_BARRIER(0);
+    SR_VM_BARRIER(8);
     __builtin_amdgcn_sched_barrier(0);
     // Quarter 2 with the A rows of step t + 2 and the next step's quarter-0
     // fragments (after the last step a stale buffer that is never used):
@@ -682,12 +751,23 @@ gemm_dma_kernel(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict_
       }
     }
   };
-  for (int t = 0; t < nk; t += 3) {
-    // B ring slots: t % 3 with three (t is a multiple of 3 here), t % 2 with two
-    const int s0 = BRING == 3 ? 0 : (t & 1), s1 = BRING == 3 ? 1 : s0 ^ 1, s2 = BRING == 3 ? 2 : s0;
-    step(t, s0, s1, a0, b0, a1, b1, a2, b2);
-    if (t + 1 < nk) step(t + 1, s1, s2, a1, b1, a2, b2, a0, b0);
-    if (t + 2 < nk) step(t + 2, s2, BRING == 3 ? 0 : s1, a2, b2, a0, b0, a1, b1);
+  if constexpr (BRING == 3) {
+    for (int t = 0; t < nk; t += 3) {  // B ring slot t % 3
+      step(t, 0, 1, a0, b0, a1, b1, a2, b2);
+      if (t + 1 < nk) step(t + 1, 1, 2, a1, b1, a2, b2, a0, b0);
+      if (t + 2 < nk) step(t + 2, 2, 0, a2, b2, a0, b0, a1, b1);
+    }
+  } else {
+    int sa = 0;  // slot of A_t
+    auto next = [&] { sa = sa >= 3 ? sa - 3 : sa + 2; };
+    for (int t = 0; t < nk; t += 3) {
+      step5(t, sa, a0, b0, a1, b1, a2, b2);
+      next();
+      if (t + 1 < nk) step5(t + 1, sa, a1, b1, a2, b2, a0, b0);
+      next();
+      if (t + 2 < nk) step5(t + 2, sa, a2, b2, a0, b0, a1, b1);
+      next();
+    }
   }
   // no DMA may still be writing LDS and no wave still reading it
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
