@@ -9,7 +9,7 @@
 // their lanes (used by the fp32 model).
 // Split-K writes fp32 partials [split][M][Nout] that a consumer sums in
 // split order, so results do not depend on scheduling.
-#include <cstdlib>
+#include <algorithm>
 #include <type_traits>
 
 #include "common.h"
@@ -482,48 +482,244 @@ gemm_big_kernel(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict_
 }
 
 
+// s_waitcnt vmcnt(N) lgkmcnt(0) then s_barrier, N a compile-time count.
+template <int N>
+__device__ __forceinline__ void vm_barrier() {
+  static_assert(N >= 0 && N <= 63, "vmcnt range");
+#define SR_VMB_CASE(n) \
+  if constexpr (N == n) asm volatile("s_waitcnt vmcnt(" #n ") lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  SR_VMB_CASE(0) SR_VMB_CASE(1) SR_VMB_CASE(2) SR_VMB_CASE(3) SR_VMB_CASE(4) SR_VMB_CASE(5) SR_VMB_CASE(6)
+  SR_VMB_CASE(7) SR_VMB_CASE(8) SR_VMB_CASE(9) SR_VMB_CASE(10) SR_VMB_CASE(11) SR_VMB_CASE(12)
+  SR_VMB_CASE(13) SR_VMB_CASE(14) SR_VMB_CASE(15) SR_VMB_CASE(16) SR_VMB_CASE(17) SR_VMB_CASE(18)
+  SR_VMB_CASE(19) SR_VMB_CASE(20) SR_VMB_CASE(21) SR_VMB_CASE(22) SR_VMB_CASE(23) SR_VMB_CASE(24)
+  SR_VMB_CASE(25) SR_VMB_CASE(26) SR_VMB_CASE(27) SR_VMB_CASE(28) SR_VMB_CASE(29) SR_VMB_CASE(30)
+  SR_VMB_CASE(31) SR_VMB_CASE(32) SR_VMB_CASE(33) SR_VMB_CASE(34) SR_VMB_CASE(35) SR_VMB_CASE(36)
+  SR_VMB_CASE(37) SR_VMB_CASE(38) SR_VMB_CASE(39) SR_VMB_CASE(40) SR_VMB_CASE(41) SR_VMB_CASE(42)
+  SR_VMB_CASE(43) SR_VMB_CASE(44) SR_VMB_CASE(45) SR_VMB_CASE(46) SR_VMB_CASE(47) SR_VMB_CASE(48)
+  SR_VMB_CASE(49) SR_VMB_CASE(50) SR_VMB_CASE(51) SR_VMB_CASE(52) SR_VMB_CASE(53) SR_VMB_CASE(54)
+  SR_VMB_CASE(55) SR_VMB_CASE(56) SR_VMB_CASE(57) SR_VMB_CASE(58) SR_VMB_CASE(59) SR_VMB_CASE(60)
+  SR_VMB_CASE(61) SR_VMB_CASE(62) SR_VMB_CASE(63)
+#undef SR_VMB_CASE
+}
+
 // ------------------------------------- bf16 MFMA GEMM, LDS-DMA pipeline
-// 256 x 256 block tile (PAIRED: gate and up rows interleaved in groups of 32,
-// 128 output columns), K step 64, two LDS stages of 64 KB.  Operand tiles go
+// Block tile of 64 TI x 64 TI (PAIRED: gate and up rows interleaved in groups
+// of 32, half as many output columns), K step 64, 4 waves of a 32 TI x 32 TI
+// tile of TI x TI v_mfma_f32_32x32x16_bf16 accumulators.  Operand tiles go
 // from memory straight into LDS with buffer loads (buffer_load_dwordx4 ...
 // lds: no staging registers, the K step as the scalar offset, 1-4 % faster
-// than global_load_lds_dwordx4 with 64-bit lane addresses); each
-// instruction moves 8 rows of 128 bytes, so every request to L2 is a whole
-// 128-byte line.  A K step is four quarter steps of 16
-// MFMAs per wave (4 waves, each a 128 x 128 tile of 4 x 4
-// v_mfma_f32_32x32x16_bf16 accumulators).  The fragments of quarters 1-3
-// are read under the MFMAs of quarters 0 and 1 (three register sets that
-// rotate from step to step), so the buffer is free after quarter 1: the
-// DMAs of the step after next are spread over quarters 2 and 3 (A rows, then
-// B rows), which keeps the vector-memory path from backing up into the MFMA
-// issue.  One barrier per step, after quarter 1: the buffer has been read by
-// all waves and the next step (whose DMAs went out under quarters 2 and 3 of
-// the step before) has landed in all of them.  LDS rows hold eight
-// 16-byte chunks; chunk c of tile row r sits in slot c ^ (r & 7) ^ ((r >> 3) & 3)
-// (a function of r mod 32, so fragment blocks of 32 rows share it), which puts the fragment reads of any 8 or 16 consecutive rows on distinct
-// banks.
-#define SR_VM_BARRIER(n) asm volatile("s_waitcnt vmcnt(" #n ") lgkmcnt(0)\n\ts_barrier" ::: "memory")
-
+// than global_load_lds_dwordx4 with 64-bit lane addresses); each instruction
+// moves 8 rows of 128 bytes, so every request to L2 is a whole 128-byte line.
 //
-// BRING = 3 (a few hundred rows, where every weight tile comes from HBM and
-// is shared by few row tiles): the weight rows get a ring of three buffers
-// of their own, filled three steps ahead, while the activation rows (in L2)
-// keep two; 160 KB of LDS.
-template <bool PAIRED, int BRING>
+// The rows of A and of B of the K steps take turns in five LDS slots (A_t in
+// slot 2 t mod 5, B_t in the one after).  A K step is four quarters of TI^2
+// MFMAs per wave; the fragments of quarters 1-3 are read under the MFMAs of
+// quarters 0 and 1 (three register sets that rotate from step to step).  The
+// slot of B_(t-1) is free from the start of step t and takes A_(t+2) under
+// quarters 0 and 1; the one barrier of the step, after quarter 1, frees the
+// slots of step t (read by all waves) and finds step t + 1 landed; B_(t+2)
+// then goes to the slot of A_t under quarters 2 and 3.  So the copies spread
+// over the whole step: with two stages of both operands they all went out
+// under two quarters, which backed up the copy path into the MFMA issue (8B
+// layer at 32768 rows: 11.26 -> 10.98 ms).
+//
+// LDS rows hold eight 16-byte chunks; chunk c of tile row r sits in slot
+// c ^ (r & 7) ^ ((r >> 3) & 3) (a function of r mod 32, so fragment blocks of
+// 32 rows share it), which puts the fragment reads of any 8 or 16 consecutive
+// rows on distinct banks.
+//
+// TI 4 (256 x 256, 160 KB of LDS, one work-group a CU) reads 8 KB of fragments
+// per 16 MFMAs; TI 2 (128 x 128, 80 KB, two work-groups a CU) 4 KB per 4, but
+// leaves less of a small grid's last round empty.
+template <bool PAIRED, int TI>
+__global__ void __launch_bounds__(256, TI == 2 ? 2 : 1)
+gemm_slots_kernel(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ B, int ldb,
+                  int64_t pair_off, int M, int N, int K, int k_per_split, EpiArgs epi,
+                  float* __restrict__ partial) {
+  constexpr int BM = 64 * TI, BK = 64;
+  constexpr int BN_OUT = PAIRED ? BM / 2 : BM;
+  constexpr int HALF = BM * BK;  // bf16 elements of the A (or B) rows of a K step
+  constexpr int D = 2 * TI;      // copies per wave of a slot
+  constexpr int NP = TI * TI / 2;  // MFMA pairs of a quarter
+  __shared__ __attribute__((aligned(1024))) bf16_t lds[5 * HALF];
+
+  const TileIdx tile = tile_of((M + BM - 1) / BM, (N + BN_OUT - 1) / BN_OUT, K / k_per_split);
+  if (!tile.valid) return;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm0 = (wave >> 1) * 32 * TI, wn0 = (wave & 1) * 32 * TI;
+  const int m0 = tile.m * BM, n0 = tile.n * BN_OUT;
+  const int k_begin = tile.split * k_per_split;
+  const int nk = k_per_split / BK;
+
+  // Copy sources: wave w moves rows 8 (w + 4 i) .. + 7, i < D.  Lane l writes
+  // slot l % 8 of row l / 8, so it fetches the chunk stored there.  Rows past
+  // M or N are clamped (their results are never stored).
+  uint32_t aoff[D], boff[D];
+#pragma unroll
+  for (int i = 0; i < D; ++i) {
+    const int r = 8 * (wave + 4 * i) + (lane >> 3);
+    const int c = (lane & 7) ^ (r & 7) ^ ((r >> 3) & 3);
+    aoff[i] = (uint32_t)(((int64_t)min(m0 + r, M - 1) * lda + c * 8) * 2);
+    int n;
+    int64_t off = 0;
+    if (PAIRED) {
+      const int grp = r >> 5;
+      n = n0 + (grp >> 1) * 32 + (r & 31);
+      off = (grp & 1) * pair_off;
+    } else {
+      n = n0 + r;
+    }
+    boff[i] = (uint32_t)((off + (int64_t)min(n, N - 1) * ldb + c * 8) * 2);
+  }
+  const BufRsrc ra = buf_rsrc(A + k_begin), rb = buf_rsrc(B + k_begin);
+  bf16_t* const dst0 = lds + wave * 512;
+  auto copy = [&](bool b, int i, int st, int slot) {
+    dma16(b ? rb : ra, b ? boff[i] : aoff[i], st * BK * 2, dst0 + slot * HALF + 2048 * i);
+  };
+  auto copy_all = [&](bool b, int st, int slot) {
+#pragma unroll
+    for (int i = 0; i < D; ++i) copy(b, i, st, slot);
+  };
+
+  // Fragment reads: lane l holds row l % 32 of a 32-row block, K chunk
+  // 2 q + l / 32 of quarter q.
+  const int fr = lane & 31, fg = lane >> 5;
+  const int sw = (fr & 7) ^ ((fr >> 3) & 3);
+  int foff[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) foff[q] = fr * BK + 8 * ((2 * q + fg) ^ sw);
+  auto frag = [](const bf16_t* p, int i) { return *reinterpret_cast<const bf16x8*>(p + 32 * i * BK); };
+
+  f32x16 acc[TI][TI];
+#pragma unroll
+  for (int i = 0; i < TI; ++i)
+#pragma unroll
+    for (int j = 0; j < TI; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+  auto mfma2 = [&](int p, const bf16x8(&af)[TI], const bf16x8(&bfr)[TI]) {
+    const int i = 2 * p / TI, j = 2 * p % TI;
+    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[j], af[i], acc[i][j], 0, 0, 0);
+    acc[i][j + 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[j + 1], af[i], acc[i][j + 1], 0, 0, 0);
+  };
+
+  // Every step issues the copies of the step after next; past the last step
+  // the source is clamped to the last step (data never read), which keeps
+  // every wait the same.
+  copy_all(false, 0, 0);
+  copy_all(true, 0, 1);
+  copy_all(false, min(1, nk - 1), 2);
+  copy_all(true, min(1, nk - 1), 3);
+  vm_barrier<2 * D>();
+  __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): no scalar loads in flight past here
+  bf16x8 a0[TI], b0[TI], a1[TI], b1[TI], a2[TI], b2[TI];
+#pragma unroll
+  for (int i = 0; i < TI; ++i) {
+    a0[i] = frag(lds + wm0 * BK + foff[0], i);
+    b0[i] = frag(lds + HALF + wn0 * BK + foff[0], i);
+  }
+  // One K step with its quarter 0 in (xa, xb); quarter 3 reuses those
+  // registers and the next step's quarter 0 goes to (ya, yb).  sa: slot of
+  // A_t.  The order of MFMAs, fragment reads and copies is written out: left
+  // alone, the scheduler bunches the copies behind one MFMA.
+  auto step = [&](int t, int sa, bf16x8(&xa)[TI], bf16x8(&xb)[TI], bf16x8(&ya)[TI], bf16x8(&yb)[TI],
+                  bf16x8(&za)[TI], bf16x8(&zb)[TI]) {
+    auto slot = [&](int k) { return sa + k >= 5 ? sa + k - 5 : sa + k; };
+    const int st = min(t + 2, nk - 1);
+    const bf16_t* ar = lds + sa * HALF + wm0 * BK;
+    const bf16_t* br = lds + slot(1) * HALF + wn0 * BK;
+    const bf16_t* an = lds + slot(2) * HALF + wm0 * BK + foff[0];
+    const bf16_t* bn = lds + slot(3) * HALF + wn0 * BK + foff[0];
+    const int fifth = slot(4);
+    // share p of NP of n things: f(k) for k in [p n / NP, (p + 1) n / NP)
+    auto share = [](int p, int n, auto&& f) {
+#pragma unroll
+      for (int k = p * n / NP; k < (p + 1) * n / NP; ++k) f(k);
+    };
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      mfma2(p, xa, xb);
+      share(p, 4 * TI, [&](int k) {
+        if (k < TI) ya[k] = frag(ar + foff[1], k);
+        else if (k < 2 * TI) yb[k - TI] = frag(br + foff[1], k - TI);
+        else if (k < 3 * TI) za[k - 2 * TI] = frag(ar + foff[2], k - 2 * TI);
+        else zb[k - 3 * TI] = frag(br + foff[2], k - 3 * TI);
+      });
+      share(p, D / 2, [&](int k) { copy(false, k, st, fifth); });
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      mfma2(p, ya, yb);
+      share(p, 2 * TI, [&](int k) {
+        if (k < TI) xa[k] = frag(ar + foff[3], k);
+        else xb[k - TI] = frag(br + foff[3], k - TI);
+      });
+      share(p, D / 2, [&](int k) { copy(false, D / 2 + k, st, fifth); });
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    // step t has been read by all waves; step t + 1 landed (all but this
+    // wave's newest copies, the A rows of step t + 2)
+    vm_barrier<D>();
+    __builtin_amdgcn_sched_barrier(0);
+    // (after the last step the next quarter 0 is a stale slot, never used)
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      mfma2(p, za, zb);
+      share(p, 2 * TI, [&](int k) {
+        if (k < TI) ya[k] = frag(an, k);
+        else yb[k - TI] = frag(bn, k - TI);
+      });
+      share(p, D / 2, [&](int k) { copy(true, k, st, sa); });
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      mfma2(p, xa, xb);
+      share(p, D / 2, [&](int k) { copy(true, D / 2 + k, st, sa); });
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  int sa = 0;  // slot of A_t
+  auto next = [&] { sa = sa >= 3 ? sa - 3 : sa + 2; };
+  for (int t = 0; t < nk; t += 3) {
+    step(t, sa, a0, b0, a1, b1, a2, b2);
+    next();
+    if (t + 1 < nk) step(t + 1, sa, a1, b1, a2, b2, a0, b0);
+    next();
+    if (t + 2 < nk) step(t + 2, sa, a2, b2, a0, b0, a1, b1);
+    next();
+  }
+  // no copy may still be writing LDS and no wave still reading it
+  vm_barrier<0>();
+  float* st = reinterpret_cast<float*>(lds) + wave * (TI == 4 ? 8192 : 4096);
+  if (PAIRED && !partial)
+    tile_epilogue_32<TI, TI, PAIRED, PAIRED>(acc, st, lane, m0 + wm0, n0 + wn0 / 2, M, N, tile.split, epi, partial);
+  else
+    tile_epilogue_32<TI, TI, PAIRED, false>(acc, st, lane, m0 + wm0, n0 + (PAIRED ? wn0 / 2 : wn0), M, N, tile.split,
+                                            epi, partial);
+}
+
+// --------------------- bf16 MFMA GEMM, a few hundred rows, many columns
+// 256 x 256 tile with the K steps, quarters and LDS rows of gemm_slots_kernel
+// for a few hundred rows, where every weight tile comes from HBM and is
+// shared by few row tiles: the weight rows get a ring of three buffers,
+// filled three steps ahead, the activation rows (in L2) one of two; 160 KB
+// of LDS.  The A rows of step t + 2 go out under quarter 2, the B rows of step
+// t + 3 under quarter 3.
+template <bool PAIRED>
 __global__ void __launch_bounds__(256)
-gemm_dma_kernel(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ B, int ldb,
+gemm_ring3_kernel(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ B, int ldb,
                 int64_t pair_off, int M, int N, int K, int k_per_split, EpiArgs epi,
                 float* __restrict__ partial) {
   constexpr int BM = 256, BNL = 256, BK = 64;
   constexpr int BN_OUT = PAIRED ? 128 : 256;
   constexpr int HALF = BM * BK;           // bf16 elements of the A (or B) rows of a K step
-  static_assert(BM == BNL, "A and B rows share the slots");
-  static_assert(BRING == 2 || BRING == 3, "weight ring depth");
   __shared__ __attribute__((aligned(1024))) bf16_t lds[5 * HALF];
-  // BRING 3: A rows of ring slot `a`, B rows of ring slot `b`; BRING 2: five
-  // slots for A and B rows alike
+  // A rows of ring slot `a` of two, B rows of ring slot `b` of three
   auto a_base = [&](int a) { return lds + a * HALF; };
-  auto b_base = [&](int b) { return lds + (BRING == 2 ? b * HALF : 2 * HALF + b * HALF); };
+  auto b_base = [&](int b) { return lds + (2 + b) * HALF; };
 
   const TileIdx tile = tile_of((M + BM - 1) / BM, (N + BN_OUT - 1) / BN_OUT, K / k_per_split);
   if (!tile.valid) return;
@@ -618,99 +814,26 @@ gemm_dma_kernel(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict_
   // Every step issues the DMAs of the step after next; past the last step
   // the source is clamped to the last step (data never read), which keeps
   // every wait below the same at each step.
-  if constexpr (BRING == 3) {
-    issue_half(0, 0, 0);
-    issue_half(0, 0, 1);
-    issue_half(min(1, nk - 1), 1, 0);
-    issue_half(min(1, nk - 1), 1, 1);
-    issue_half(min(2, nk - 1), 2, 1);
-    SR_VM_BARRIER(24);
-  } else {
-    issue_half(0, 0, 0);
-    issue_half(0, 1, 1);
-    issue_half(min(1, nk - 1), 2, 0);
-    issue_half(min(1, nk - 1), 3, 1);
-    SR_VM_BARRIER(16);
-  }
+  issue_half(0, 0, 0);
+  issue_half(0, 0, 1);
+  issue_half(min(1, nk - 1), 1, 0);
+  issue_half(min(1, nk - 1), 1, 1);
+  issue_half(min(2, nk - 1), 2, 1);
+  vm_barrier<24>();
   __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): no scalar loads in flight past here
   bf16x8 a0[4], b0[4], a1[4], b1[4], a2[4], b2[4];
-  read_frags(0, BRING == 3 ? 0 : 1, 0, a0, b0);
-  auto mfma2 = [&](int p, const bf16x8(&af)[4], const bf16x8(&bfr)[4]) {
-    const int i = p >> 1, j = (p & 1) * 2;
-    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[j], af[i], acc[i][j], 0, 0, 0);
-    acc[i][j + 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[j + 1], af[i], acc[i][j + 1], 0, 0, 0);
-  };
-  // BRING 2.  The rows of A and of B of the steps take turns in five slots of
-  // 32 KB (A_t in slot 2 t mod 5, B_t in the one after), so the copies spread
-  // over the whole step: the slot of B_(t-1) is free from the start of step t
-  // and takes A_(t+2) under quarters 0 and 1; the barrier after quarter 1
-  // frees the slots of step t and B_(t+2) goes to that of A_t under quarters
-  // 2 and 3.  One copy per four MFMAs; with two stages of both they all had to
-  // go out under two quarters, which filled the copy path and held up the
-  // MFMA issue behind it.  sa: slot of A_t.
-  auto step5 = [&](int t, int sa, bf16x8(&xa)[4], bf16x8(&xb)[4], bf16x8(&ya)[4], bf16x8(&yb)[4], bf16x8(&za)[4],
-                   bf16x8(&zb)[4]) {
-    auto slot = [&](int k) { return sa + k >= 5 ? sa + k - 5 : sa + k; };
-    const int koff = min(t + 2, nk - 1) * BK * 2;
-    const bf16_t* ar = a_base(sa) + wm0 * BK;
-    const bf16_t* br = b_base(slot(1)) + wn0 * BK;
-    const bf16_t* an = a_base(slot(2)) + wm0 * BK + foff[0];
-    const bf16_t* bn = b_base(slot(3)) + wn0 * BK + foff[0];
-    bf16_t* ad = a_base(slot(4)) + wave * 512;
-    bf16_t* bd = b_base(sa) + wave * 512;
-    auto frag = [](const bf16_t* p, int i) { return *reinterpret_cast<const bf16x8*>(p + 32 * i * BK); };
-#pragma unroll
-    for (int p = 0; p < 8; ++p) {
-      mfma2(p, xa, xb);
-      if (p < 4) {
-        ya[p] = frag(ar + foff[1], p);
-        yb[p] = frag(br + foff[1], p);
-      } else {
-        za[p - 4] = frag(ar + foff[2], p - 4);
-        zb[p - 4] = frag(br + foff[2], p - 4);
-      }
-      if (p & 1) dma16(ra, aoff[p >> 1], koff, ad + 2048 * (p >> 1));
-      __builtin_amdgcn_sched_barrier(0);
-    }
-#pragma unroll
-    for (int p = 0; p < 8; ++p) {
-      mfma2(p, ya, yb);
-      if (p < 4) xa[p] = frag(ar + foff[3], p);
-      else xb[p - 4] = frag(br + foff[3], p - 4);
-      if (p & 1) dma16(ra, aoff[4 + (p >> 1)], koff, ad + 2048 * (4 + (p >> 1)));
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    // step t has been read by all waves; step t + 1 landed (all but this
-    // wave's newest copies, the A rows of step t + 2)
-    SR_VM_BARRIER(8);
-    __builtin_amdgcn_sched_barrier(0);
-    // (after the last step the next quarter 0 is a stale buffer, never used)
-#pragma unroll
-    for (int p = 0; p < 8; ++p) {
-      mfma2(p, za, zb);
-      if (p < 4) ya[p] = frag(an, p);
-      else yb[p - 4] = frag(bn, p - 4);
-      if (p & 1) dma16(rb, boff[p >> 1], koff, bd + 2048 * (p >> 1));
-      __builtin_amdgcn_sched_barrier(0);
-    }
-#pragma unroll
-    for (int p = 0; p < 8; ++p) {
-      mfma2(p, xa, xb);
-      if (p & 1) dma16(rb, boff[4 + (p >> 1)], koff, bd + 2048 * (4 + (p >> 1)));
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  };
+  read_frags(0, 0, 0, a0, b0);
   // One K step with its quarter 0 in (xa, xb); quarter 3 reuses those
   // registers and the next step's quarter 0 goes to (ya, yb).  bb, bbn: B
   // ring slots of steps t and t + 1.  One barrier per step, after quarter 1:
   // every wave has read the buffers of step t, and step t + 1 has landed
   // (all but this wave's newest DMAs: none with two stages, the B rows of
   // step t + 2 with three).  Then the A rows of step t + 2 go out under
-  // quarter 2 and the B rows of step t + BRING under quarter 3.
+  // quarter 2 and the B rows of step t + 3 under quarter 3.
   auto step = [&](int t, int bb, int bbn, bf16x8(&xa)[4], bf16x8(&xb)[4], bf16x8(&ya)[4], bf16x8(&yb)[4],
                   bf16x8(&za)[4], bf16x8(&zb)[4]) {
     const int buf = t & 1;
-    const int nx = min(t + 2, nk - 1), nxb = min(t + BRING, nk - 1);
+    const int nx = min(t + 2, nk - 1), nxb = min(t + 3, nk - 1);
     read_frags(buf, bb, 1, ya, yb);
     read_frags(buf, bb, 2, za, zb);
     mfma(xa, xb);
@@ -718,7 +841,7 @@ gemm_dma_kernel(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict_
     read_frags(buf, bb, 3, xa, xb);
     mfma(ya, yb);
     reads8();
-    SR_VM_BARRIER(8);
+    vm_barrier<8>();
     __builtin_amdgcn_sched_barrier(0);
     // Quarter 2 with the A rows of step t + 2 and the next step's quarter-0
     // fragments (after the last step a stale buffer that is never used):
@@ -738,7 +861,7 @@ gemm_dma_kernel(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict_
         __builtin_amdgcn_sched_barrier(0);
       }
     }
-    // Quarter 3 with the B rows of step t + BRING, one copy per MFMA pair.
+    // Quarter 3 with the B rows of step t + 3, one copy per MFMA pair.
     {
       bf16_t* dst = b_base(bb);
 #pragma unroll
@@ -751,23 +874,10 @@ gemm_dma_kernel(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict_
       }
     }
   };
-  if constexpr (BRING == 3) {
-    for (int t = 0; t < nk; t += 3) {  // B ring slot t % 3
-      step(t, 0, 1, a0, b0, a1, b1, a2, b2);
-      if (t + 1 < nk) step(t + 1, 1, 2, a1, b1, a2, b2, a0, b0);
-      if (t + 2 < nk) step(t + 2, 2, 0, a2, b2, a0, b0, a1, b1);
-    }
-  } else {
-    int sa = 0;  // slot of A_t
-    auto next = [&] { sa = sa >= 3 ? sa - 3 : sa + 2; };
-    for (int t = 0; t < nk; t += 3) {
-      step5(t, sa, a0, b0, a1, b1, a2, b2);
-      next();
-      if (t + 1 < nk) step5(t + 1, sa, a1, b1, a2, b2, a0, b0);
-      next();
-      if (t + 2 < nk) step5(t + 2, sa, a2, b2, a0, b0, a1, b1);
-      next();
-    }
+  for (int t = 0; t < nk; t += 3) {  // B ring slot t % 3
+    step(t, 0, 1, a0, b0, a1, b1, a2, b2);
+    if (t + 1 < nk) step(t + 1, 1, 2, a1, b1, a2, b2, a0, b0);
+    if (t + 2 < nk) step(t + 2, 2, 0, a2, b2, a0, b0, a1, b1);
   }
   // no DMA may still be writing LDS and no wave still reading it
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
@@ -778,7 +888,6 @@ gemm_dma_kernel(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict_
     tile_epilogue_32<4, 4, PAIRED, false>(acc, st, lane, m0 + wm0, n0 + (PAIRED ? wn0 / 2 : wn0), M, N, tile.split,
                                           epi, partial);
 }
-#undef SR_VM_BARRIER
 
 
 // ------------------------- bf16 MFMA GEMM, a few hundred rows (LDS DMA)
@@ -927,27 +1036,8 @@ gemm_dma3_kernel(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict
 }
 #undef SR_VMB3
 
-// s_waitcnt vmcnt(N) lgkmcnt(0) then s_barrier, N a compile-time count; and
-// the same with N = A * D for a run-time a <= A (copies of a later stages of
+// vm_barrier with N = A * D for a run-time a <= A (copies of a later stages of
 // D instructions each may stay in flight).
-template <int N>
-__device__ __forceinline__ void vm_barrier() {
-  static_assert(N >= 0 && N <= 63, "vmcnt range");
-#define SR_VMB_CASE(n) \
-  if constexpr (N == n) asm volatile("s_waitcnt vmcnt(" #n ") lgkmcnt(0)\n\ts_barrier" ::: "memory");
-  SR_VMB_CASE(0) SR_VMB_CASE(1) SR_VMB_CASE(2) SR_VMB_CASE(3) SR_VMB_CASE(4) SR_VMB_CASE(5) SR_VMB_CASE(6)
-  SR_VMB_CASE(7) SR_VMB_CASE(8) SR_VMB_CASE(9) SR_VMB_CASE(10) SR_VMB_CASE(11) SR_VMB_CASE(12)
-  SR_VMB_CASE(13) SR_VMB_CASE(14) SR_VMB_CASE(15) SR_VMB_CASE(16) SR_VMB_CASE(17) SR_VMB_CASE(18)
-  SR_VMB_CASE(19) SR_VMB_CASE(20) SR_VMB_CASE(21) SR_VMB_CASE(22) SR_VMB_CASE(23) SR_VMB_CASE(24)
-  SR_VMB_CASE(25) SR_VMB_CASE(26) SR_VMB_CASE(27) SR_VMB_CASE(28) SR_VMB_CASE(29) SR_VMB_CASE(30)
-  SR_VMB_CASE(31) SR_VMB_CASE(32) SR_VMB_CASE(33) SR_VMB_CASE(34) SR_VMB_CASE(35) SR_VMB_CASE(36)
-  SR_VMB_CASE(37) SR_VMB_CASE(38) SR_VMB_CASE(39) SR_VMB_CASE(40) SR_VMB_CASE(41) SR_VMB_CASE(42)
-  SR_VMB_CASE(43) SR_VMB_CASE(44) SR_VMB_CASE(45) SR_VMB_CASE(46) SR_VMB_CASE(47) SR_VMB_CASE(48)
-  SR_VMB_CASE(49) SR_VMB_CASE(50) SR_VMB_CASE(51) SR_VMB_CASE(52) SR_VMB_CASE(53) SR_VMB_CASE(54)
-  SR_VMB_CASE(55) SR_VMB_CASE(56) SR_VMB_CASE(57) SR_VMB_CASE(58) SR_VMB_CASE(59) SR_VMB_CASE(60)
-  SR_VMB_CASE(61) SR_VMB_CASE(62) SR_VMB_CASE(63)
-#undef SR_VMB_CASE
-}
 template <int D, int A>
 __device__ __forceinline__ void vm_barrier_ahead(int a) {
   if constexpr (A <= 0) {
@@ -1456,24 +1546,67 @@ gemm_f32_kernel(const float* __restrict__ A, int lda, const float* __restrict__ 
   }
 }
 
-// Sum split-K partials in split order, then apply the epilogue.
-__global__ void gemm_reduce_kernel(const float* __restrict__ partial, int splits, int M, int N,
-                                   int paired, EpiArgs epi) {
-  const int nout = paired ? 2 * N : N;
-  const int64_t total = (int64_t)M * N;
-  for (int64_t idx = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; idx < total;
-       idx += (int64_t)gridDim.x * blockDim.x) {
-    int m = (int)(idx / N), n = (int)(idx % N);
-    float g = 0.f, u = 0.f;
-    for (int s = 0; s < splits; ++s) {
-      const float* p = partial + ((int64_t)s * M + m) * nout;
-      g += p[n];
-      if (paired) u += p[N + n];
+// Sum split-K partials in split order, then apply the epilogue.  Four columns
+// a thread (VEC: 16-byte aligned rows of a multiple of 4 columns), all splits
+// of them loaded together (up to eight); grid (column blocks, rows).
+template <bool VEC>
+__global__ void __launch_bounds__(256)
+gemm_reduce_kernel(const float* __restrict__ partial, int splits, int M, int N, int paired, EpiArgs epi) {
+  const int n = 4 * (blockIdx.x * 256 + threadIdx.x);
+  if (n >= N) return;
+  const int64_t nout = paired ? 2 * (int64_t)N : (int64_t)N;
+  for (int m = blockIdx.y; m < M; m += gridDim.y) {
+    const float* p = partial + (int64_t)m * nout + n;
+    const int64_t ss = M * nout;
+    auto sum = [&](const float* q) {
+      f32x4 v[8];
+#pragma unroll
+      for (int s = 0; s < 8; ++s) {
+        v[s] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (s >= splits) continue;
+        if constexpr (VEC) {
+          v[s] = *reinterpret_cast<const f32x4*>(q + s * ss);
+        } else {
+#pragma unroll
+          for (int k = 0; k < 4; ++k)
+            if (n + k < N) v[s][k] = q[s * ss + k];
+        }
+      }
+      f32x4 a = v[0];
+#pragma unroll
+      for (int s = 1; s < 8; ++s)
+        if (s < splits) a += v[s];
+      for (int s = 8; s < splits; ++s) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          if (n + k < N) a[k] += q[s * ss + k];
+      }
+      return a;
+    };
+    f32x4 g = sum(p);
+    if (paired) {
+      const f32x4 u = sum(p + N);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) g[k] = silu(g[k]) * u[k];
     }
-    if (paired)
-      store_out(epi, m, n, silu(g) * u);
-    else
-      epi_one(epi, m, n, g);
+    if constexpr (VEC) {
+      const int64_t off = (int64_t)m * epi.ldo + n;
+      if (!paired && epi.mode == EPI_RESID) {
+        float* h = reinterpret_cast<float*>(epi.out) + off;
+        store4(h, *reinterpret_cast<const f32x4*>(h) + g);
+      } else if (epi.out_bf16) {
+        store4(reinterpret_cast<bf16_t*>(epi.out) + off, g);
+      } else {
+        store4(reinterpret_cast<float*>(epi.out) + off, g);
+      }
+    } else {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        if (n + k >= N) break;
+        if (paired) store_out(epi, m, n + k, g[k]);
+        else epi_one(epi, m, n + k, g[k]);
+      }
+    }
   }
 }
 
@@ -1490,48 +1623,100 @@ static void launch_bf16(const GemmArgs& g, int splits, int kps, const EpiArgs& e
 }
 
 size_t gemm_partial_elems(int dtype, int M, int N, int K, bool paired) {
-  GemmPlan p = gemm_plan(dtype, M, N, K, paired);
+  GemmPlan p = gemm_plan(dtype, M, N, K, paired, false);
   if (p.splits <= 1 && dtype == SR_BF16) return 0;
   return (size_t)p.splits * M * (paired ? 2 * (size_t)N : (size_t)N);
 }
 
-// Partials needed by an EPI_PARTIAL call (written even without a K split).
-size_t gemm_partial_elems_always(int dtype, int M, int N, int K) {
-  GemmPlan p = gemm_plan(dtype, M, N, K, false);
-  return (size_t)p.splits * M * (size_t)N;
+// The plan is the same for all rows within each of (0, 32], (32, 64],
+// (64, 112], (112, 128] and every further 128, so the most partials are needed
+// at the end of one.
+size_t gemm_partial_elems_upto(int dtype, int M_max, int N, int K, bool paired, bool fused) {
+  size_t most = 0;
+  auto at = [&](int M) {
+    if (fused) most = std::max(most, (size_t)gemm_plan(dtype, M, N, K, paired, true).splits * M * (size_t)N);
+    else most = std::max(most, gemm_partial_elems(dtype, M, N, K, paired));
+  };
+  for (int M : {32, 64, 112})
+    if (M < M_max) at(M);
+  for (int M = 128; M < M_max; M += 128) at(M);
+  if (M_max > 0) at(M_max);
+  return most;
 }
 
 // Dispatch thresholds (rows M of the projection), measured on MI355X:
 //  - up to kStreamMaxRows rows the LDS-DMA streaming kernel (weights read
 //    once, one work-group per CU);
-//  - up to kDma3MaxRows rows the 256 x 256 tile with the three-deep weight
-//    ring when its grid holds at least kDmaWideMinTiles tiles, else the
-//    three-stage 256 x 128 tile;
-//  - from kDmaMinRows rows (or 256 rows with kDmaWideMinTiles tiles) the
-//    LDS-DMA 256 x 256 tile, and the register-staged 256 x 256 tile when
-//    an operand is too large for 32-bit buffer offsets.
+//  - above, the tile kernel and K split that tile_plan expects to be fastest;
+//  - the register-staged tiles when an operand is too large for 32-bit buffer
+//    offsets.
 constexpr int kStreamMaxRows = 128;
-constexpr int kDma3MaxRows = 512;
-constexpr int kDmaWideMinTiles = 192;
-constexpr int kDmaMinRows = 1024;
+constexpr int kWringMaxRows = 512;
 constexpr int kBigTileMinRows = 1024;
 constexpr int kTileRot = 7;
 
 static int stream_tile_rows(int M) { return M <= 32 ? 32 : (M <= 64 ? 64 : (M <= 112 ? 112 : 128)); }
 
-GemmPlan gemm_plan(int dtype, int M, int N, int K, bool paired) {
-  GemmPlan p;
-  p.splits = 1;
-  p.big = false;
-  p.dma = false;
-  p.dma3 = false;
-  p.dma_bring = 2;
-  p.stream = 0;
-  p.stream_bn = 0;
+// Expected time (us) of a tile kernel over M x N x K with K split `splits`
+// ways, fitted to 1700 measurements on MI355X (129-5000 rows of the 8B, 1B and
+// small shapes' projections; rms error 11 %, the choice by it on average 1.8 %
+// slower than the best of them): a start, per round of work-groups a fixed
+// part and the K steps, and the reduction of the partials.  256-column and
+// 128-column tiles run one work-group a CU; of the 128 x 128 tiles two share a
+// CU, at 0.95 us a step together against 0.62 us alone.  Rows are counted in
+// whole 128s, so the choice is the same within each.
+static double tile_cost(GemmKind kind, int M, int N, int K, bool paired, int splits) {
+  const int bm = kind == GEMM_TILE128 ? 128 : 256;
+  const int bn = (kind == GEMM_TILE128 || kind == GEMM_DMA3 ? 128 : 256) / (paired ? 2 : 1);
+  const int64_t groups = (int64_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn) * splits;
+  const double steps = K / 64 / splits;
+  const double one = (double)((groups + 255) / 256);
+  double t;
+  if (kind == GEMM_TILE128) {
+    const double full = (double)(groups / 512);
+    const int64_t rest = groups % 512;
+    t = 3.2 + (full * 0.95 + (rest == 0 ? 0.0 : (rest <= 256 ? 0.62 : 0.95))) * steps + (full + (rest > 0)) * 2.4;
+  } else if (kind == GEMM_DMA3) {
+    t = 3.2 + one * (0.69 * steps + 4.4);
+  } else {
+    t = 3.2 + one * (1.07 * steps + 8.8);
+  }
+  const double rows = (M + 127) / 128 * 128.0;
+  if (splits > 1) t += 5.0 + 0.33e-6 * 4.0 * (splits * (paired ? 2 : 1) + 1) * rows * N;
+  return t;
+}
+
+static GemmPlan tile_plan(int M, int N, int K, bool paired) {
+  GemmPlan best{GEMM_REG, 1, 0, 0};
+  if (K % 64 != 0) return best;
+  double t_best = 0.0;
+  const int64_t tiles128 = (int64_t)((M + 127) / 128) * ((N + (paired ? 63 : 127)) / (paired ? 64 : 128));
+  const int64_t tiles256 = (int64_t)((M + 255) / 256) * ((N + (paired ? 127 : 255)) / (paired ? 128 : 256));
+  for (GemmKind kind : {GEMM_TILE128, GEMM_TILE256, GEMM_DMA3})
+    for (int splits = 1; splits <= 8; splits *= 2) {
+      if (K % (splits * 64) != 0 || (splits > 1 && K / splits < 512)) break;
+      // (bounds the partials: beyond, a split would gain a few percent at most)
+      if (splits > 1 && !(tiles128 * splits < 1024 || (M > 1024 && tiles256 * splits <= 256))) break;
+      const double t = tile_cost(kind, M, N, K, paired, splits);
+      if (best.kind == GEMM_REG || t < t_best) {
+        best.kind = kind;
+        best.splits = splits;
+        t_best = t;
+      }
+    }
+  // a few hundred rows on 256 x 256 tiles: the three-deep weight ring, 2 %
+  // faster there (512 rows of the 8B gate|up projection: 104.9 against 107.1 us)
+  if (best.kind == GEMM_TILE256 && best.splits == 1 && M <= kWringMaxRows) best.kind = GEMM_WRING;
+  return best;
+}
+
+GemmPlan gemm_plan(int dtype, int M, int N, int K, bool paired, bool fused) {
+  GemmPlan p{GEMM_REG, 1, 0, 0};
   if (dtype != SR_BF16) return p;
   if (M > 64 && M <= 112 && !paired && N > 65536 && K % 128 == 0) {
     // The LM head at 65-112 rows: 112 x 128 tiles, one per work-group, with
     // the separate activation and weight rings (enough tiles without split).
+    p.kind = GEMM_STREAM;
     p.stream = 112;
     p.stream_bn = 128;
     return p;
@@ -1539,61 +1724,38 @@ GemmPlan gemm_plan(int dtype, int M, int N, int K, bool paired) {
   if (M <= kStreamMaxRows && K % 128 == 0 && (M <= 64 || N <= 65536)) {
     // One round of work-groups (one per CU): split K by the largest power of
     // two that keeps the grid within 256 and each split a multiple of 128.
+    // Where the partials need a reduction launch of their own, only if the K
+    // steps (0.7 us each) that a split saves are worth it: 4 of them at K 512
+    // are not (64 rows of the small shape's gate|up: 6.2 us and 3.6 us of
+    // reduction), 32 at K 4096 are.
+    p.kind = GEMM_STREAM;
     p.stream = stream_tile_rows(M);
     p.stream_bn = 64;
     const int64_t tiles = (int64_t)((M + p.stream - 1) / p.stream) * ((N + p.stream_bn - 1) / p.stream_bn);
-    int splits = 1;
-    while (tiles * splits * 2 <= 256 && K % (splits * 2 * 128) == 0) splits *= 2;
-    p.splits = splits;
-    return p;
-  }
-  if (M > kStreamMaxRows && M <= kDma3MaxRows && K % 64 == 0) {
-    // A few hundred rows, a grid of 256 x 256 tiles that alone fills most of
-    // the CUs: that tile with the three-deep weight ring, unsplit.
-    const int64_t wide = (int64_t)((M + 255) / 256) * ((N + (paired ? 127 : 255)) / (paired ? 128 : 256));
-    if (wide >= kDmaWideMinTiles) {
-      p.dma = true;
-      p.dma_bring = 3;
-      return p;
+    double t_best = 0.0;
+    for (int splits = 1; splits == 1 || (tiles * splits <= 256 && K % (splits * 128) == 0); splits *= 2) {
+      double t = 0.7 * (K / 128 / splits);
+      if (!fused && splits > 1) t += 5.0 + 0.33e-6 * 4.0 * (splits * (paired ? 2 : 1) + 1) * p.stream * N;
+      if (splits == 1 || t < t_best) {
+        p.splits = splits;
+        t_best = t;
+      }
     }
-    // Otherwise (the first decode round) 256 x 128 tiles with three stages;
-    // split K (each split a multiple of 64 and at least 512 long) by powers
-    // of two while the grid stays within 256.
-    p.dma3 = true;
-    const int64_t tiles = (int64_t)((M + 255) / 256) * ((N + (paired ? 63 : 127)) / (paired ? 64 : 128));
-    int splits = 1;
-    while (tiles * splits * 2 <= 256 && K % (splits * 2 * 64) == 0 && K / (splits * 2) >= 512) splits *= 2;
-    p.splits = splits;
     return p;
   }
-  const int64_t dma_tiles = (int64_t)((M + 255) / 256) * ((N + (paired ? 127 : 255)) / (paired ? 128 : 256));
-  if (K % 64 == 0 && (M >= kDmaMinRows || (M >= 256 && dma_tiles >= kDmaWideMinTiles))) {
-    // One work-group per CU at least: split K (each split a multiple of 64
-    // and at least 512 long) while the tile grid is smaller than 256.
-    p.dma = true;
-    const int64_t tiles = dma_tiles;
-    int splits = 1;
-    while (tiles * splits < 256 && K % (splits * 2 * 64) == 0 && K / (splits * 2) >= 512 && splits < 8)
-      splits *= 2;
-    p.splits = splits;
-    return p;
-  }
-  if (M >= kBigTileMinRows) {
-    p.big = true;
-    return p;
-  }
-  int bm = M <= 32 ? 32 : (M <= 64 ? 64 : 128);
+  if (M > 64) return tile_plan(M, N, K, paired);
+  // up to 64 rows with K not a multiple of 128: register-staged tiles, K split
+  // while the grid alone cannot fill 256 CUs twice over; each split keeps at
+  // least 512 of K and a multiple of 64
+  int bm = M <= 32 ? 32 : 64;
   int bn = paired ? 64 : 128;
   int64_t tiles = (int64_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn);
-  // Split K when the tile grid alone cannot fill 256 CUs twice over; each
-  // split keeps at least 512 of K and a multiple of 64.
   int splits = 1;
   while (tiles * splits < 512 && K % (splits * 2 * 64) == 0 && K / (splits * 2) >= 512 && splits < 8)
     splits *= 2;
   p.splits = splits;
   return p;
 }
-
 // The LDS-DMA kernels address their operands with 32-bit byte offsets from
 // the K base of the split; the tiled ones pass them to buffer loads as signed
 // 32-bit vector offsets, so there they stay below 2 GiB (larger operands take
@@ -1642,7 +1804,7 @@ int gemm(const GemmArgs& g, float* partial, size_t partial_cap, hipStream_t s) {
     SR_CHECK_LAUNCH();
     return 1;
   }
-  GemmPlan plan = gemm_plan(g.dtype, g.M, g.N, g.K, g.paired);
+  GemmPlan plan = gemm_plan(g.dtype, g.M, g.N, g.K, g.paired, g.epi == EPI_PARTIAL);
   const int splits = plan.splits;
   const int kps = g.K / splits;
   SR_REQUIRE(kps * splits == g.K && kps % 64 == 0, 5, "split-K must divide K into multiples of 64");
@@ -1652,7 +1814,7 @@ int gemm(const GemmArgs& g, float* partial, size_t partial_cap, hipStream_t s) {
                "GEMM partial buffer too small");
     part = partial;
   }
-  if (plan.stream && dma_offsets_fit(g)) {
+  if (plan.kind == GEMM_STREAM && dma_offsets_fit(g)) {
     dim3 grid = tile_grid((g.M + plan.stream - 1) / plan.stream, (g.N + plan.stream_bn - 1) / plan.stream_bn, splits);
 #define SR_STREAM(BM, BN, WGM, WGN, NST, P, BK, ROT)                                                    \
   SR_LAUNCH((gemm_stream_kernel<BM, BN, WGM, WGN, NST, P, BK>), grid, dim3(256), 0, s,           \
@@ -1691,32 +1853,26 @@ int gemm(const GemmArgs& g, float* partial, size_t partial_cap, hipStream_t s) {
 #undef SR_RING
 #undef SR_STREAM
     SR_CHECK_LAUNCH();
-  } else if (plan.dma3 && dma_offsets_fit(g, 31)) {
-    const int bn_out = g.paired ? 64 : 128;
-    dim3 grid = tile_grid((g.M + 255) / 256, (g.N + bn_out - 1) / bn_out, splits);
-    if (g.paired)
-      SR_LAUNCH(gemm_dma3_kernel<true>, grid, dim3(256), 0, s, (const bf16_t*)g.A, g.lda,
-                         (const bf16_t*)g.B, g.ldb, g.pair_off, g.M, g.N, g.K, kps, e, part);
-    else
-      SR_LAUNCH(gemm_dma3_kernel<false>, grid, dim3(256), 0, s, (const bf16_t*)g.A, g.lda,
-                         (const bf16_t*)g.B, g.ldb, g.pair_off, g.M, g.N, g.K, kps, e, part);
+  } else if (plan.kind >= GEMM_TILE128 && dma_offsets_fit(g, 31)) {
+    const int bm = plan.kind == GEMM_TILE128 ? 128 : 256;
+    const int bn = (plan.kind == GEMM_TILE128 || plan.kind == GEMM_DMA3 ? 128 : 256) / (g.paired ? 2 : 1);
+    dim3 grid = tile_grid((g.M + bm - 1) / bm, (g.N + bn - 1) / bn, splits);
+#define SR_TILE(KERNEL)                                                                                            \
+  SR_LAUNCH((KERNEL), grid, dim3(256), 0, s, (const bf16_t*)g.A, g.lda, (const bf16_t*)g.B, g.ldb, g.pair_off, g.M, \
+            g.N, g.K, kps, e, part)
+#define SR_TILE_P(KERNEL, ...)                                \
+  do {                                                        \
+    if (g.paired) SR_TILE((KERNEL<true __VA_ARGS__>));        \
+    else SR_TILE((KERNEL<false __VA_ARGS__>));                \
+  } while (0)
+    if (plan.kind == GEMM_TILE128) SR_TILE_P(gemm_slots_kernel, , 2);
+    else if (plan.kind == GEMM_TILE256) SR_TILE_P(gemm_slots_kernel, , 4);
+    else if (plan.kind == GEMM_WRING) SR_TILE_P(gemm_ring3_kernel);
+    else SR_TILE_P(gemm_dma3_kernel);
+#undef SR_TILE_P
+#undef SR_TILE
     SR_CHECK_LAUNCH();
-  } else if (plan.dma && dma_offsets_fit(g, 31)) {
-    const int bn_out = g.paired ? 128 : 256;
-    dim3 grid = tile_grid((g.M + 255) / 256, (g.N + bn_out - 1) / bn_out, splits);
-#define SR_DMA(P, R)                                                                                   \
-  SR_LAUNCH((gemm_dma_kernel<P, R>), grid, dim3(256), 0, s, (const bf16_t*)g.A, g.lda,        \
-                     (const bf16_t*)g.B, g.ldb, g.pair_off, g.M, g.N, g.K, kps, e, part)
-    if (plan.dma_bring == 3) {
-      if (g.paired) SR_DMA(true, 3);
-      else SR_DMA(false, 3);
-    } else {
-      if (g.paired) SR_DMA(true, 2);
-      else SR_DMA(false, 2);
-    }
-#undef SR_DMA
-    SR_CHECK_LAUNCH();
-  } else if (plan.big || plan.dma) {
+  } else if (g.M >= kBigTileMinRows) {
     const int bn_out = g.paired ? 128 : 256;
     dim3 grid = tile_grid((g.M + 255) / 256, (g.N + bn_out - 1) / bn_out, splits);
     if (g.paired)
@@ -1736,10 +1892,11 @@ int gemm(const GemmArgs& g, float* partial, size_t partial_cap, hipStream_t s) {
     else launch_bf16<128, 128, 64, 64, 64, false>(g, splits, kps, e, part, s);
   }
   if (splits > 1 && g.epi != EPI_PARTIAL) {
-    int64_t total = (int64_t)g.M * g.N;
-    int blocks = (int)std::min<int64_t>((total + 255) / 256, 8192);
-    SR_LAUNCH(gemm_reduce_kernel, dim3(blocks), dim3(256), 0, s, part, splits, g.M, g.N,
-                       (int)g.paired, e);
+    const bool vec = g.N % 4 == 0 && g.ldo % 4 == 0 && (reinterpret_cast<uintptr_t>(part) & 15) == 0 &&
+                     (reinterpret_cast<uintptr_t>(g.out) & 15) == 0;
+    const dim3 grid((g.N + 1023) / 1024, std::min(g.M, 4096));
+    if (vec) SR_LAUNCH(gemm_reduce_kernel<true>, grid, dim3(256), 0, s, part, splits, g.M, g.N, (int)g.paired, e);
+    else SR_LAUNCH(gemm_reduce_kernel<false>, grid, dim3(256), 0, s, part, splits, g.M, g.N, (int)g.paired, e);
     SR_CHECK_LAUNCH();
   }
   return splits;

@@ -167,19 +167,19 @@ static Plan make_plan(const Dims& g, const Dims& rm, int P, const sr_params* p) 
       size_t ncol = std::max({(size_t)m->qkv, (size_t)m->d, (size_t)2 * m->ff, (size_t)m->V});
       gp = std::max(gp, (size_t)Mmax * ncol);
     } else {
-      if (m == &g)
-        for (int M = 1; M <= pl.N; ++M) {
-          gp = std::max(gp, gemm_partial_elems_always(m->dtype, M, m->qkv, m->d));
-          gp = std::max(gp, gemm_partial_elems_always(m->dtype, M, m->d, m->hq * m->hd));
-          gp = std::max(gp, gemm_partial_elems_always(m->dtype, M, m->d, m->ff));
-        }
-      for (int M = 1; M <= Mmax; ++M) {
-        gp = std::max(gp, gemm_partial_elems(m->dtype, M, m->qkv, m->d, false));
-        gp = std::max(gp, gemm_partial_elems(m->dtype, M, m->d, m->hq * m->hd, false));
-        gp = std::max(gp, gemm_partial_elems(m->dtype, M, m->ff, m->d, true));
-        gp = std::max(gp, gemm_partial_elems(m->dtype, M, m->d, m->ff, false));
-        if (m == &g) gp = std::max(gp, gemm_partial_elems(m->dtype, M, m->V, m->d, false));
+      auto upto = [&](int M, int N, int K, bool paired, bool fused) {
+        gp = std::max(gp, gemm_partial_elems_upto(m->dtype, M, N, K, paired, fused));
+      };
+      if (m == &g) {
+        upto(pl.N, m->qkv, m->d, false, true);
+        upto(pl.N, m->d, m->hq * m->hd, false, true);
+        upto(pl.N, m->d, m->ff, false, true);
+        upto(Mmax, m->V, m->d, false, false);
       }
+      upto(Mmax, m->qkv, m->d, false, false);
+      upto(Mmax, m->d, m->hq * m->hd, false, false);
+      upto(Mmax, m->ff, m->d, true, false);
+      upto(Mmax, m->d, m->ff, false, false);
     }
   }
   pl.gpart = gp;

@@ -27,19 +27,28 @@ struct GemmArgs {
   int ldo;
   int out_bf16;          // EPI_STORE / paired: 1 = bf16 out, 0 = fp32 out
 };
+enum GemmKind {
+  GEMM_REG,      // register-staged tiles (K not a multiple of what the others need, operands past 2 GiB)
+  GEMM_STREAM,   // LDS-DMA streaming kernels for few rows (stream, stream_bn)
+  GEMM_TILE128,  // 128 x 128 tiles in five LDS slots, two work-groups a CU
+  GEMM_TILE256,  // 256 x 256 tiles in five LDS slots
+  GEMM_WRING,    // 256 x 256 tiles, three-deep weight ring (a few hundred rows)
+  GEMM_DMA3      // 256 x 128 tiles, three LDS stages (a few hundred rows)
+};
 struct GemmPlan {
+  GemmKind kind;
   int splits;
-  bool big;     // 256 x 256 tile kernel
-  bool dma;     // 256 x 256 tile fed by LDS DMA
-  int dma_bring;  // its weight ring depth: 2 (shared with the activations) or 3
-  bool dma3;    // 256 x 128 tile, three LDS-DMA stages (a few hundred rows)
-  int stream;     // > 0: LDS-DMA streaming kernel for few rows, tile height
+  int stream;     // GEMM_STREAM: tile height
   int stream_bn;  // its tile width (output columns)
 };
-GemmPlan gemm_plan(int dtype, int M, int N, int K, bool paired);
+// fused: the partials are summed by their consumer (EPI_PARTIAL), else by a
+// reduction launch.
+GemmPlan gemm_plan(int dtype, int M, int N, int K, bool paired, bool fused);
 size_t gemm_partial_elems(int dtype, int M, int N, int K, bool paired);
 int gemm(const GemmArgs& g, float* partial, size_t partial_cap, hipStream_t s);
-size_t gemm_partial_elems_always(int dtype, int M, int N, int K);
+// The most partials that any number of rows up to M_max needs (fused: of
+// EPI_PARTIAL calls, which write them even without a K split).
+size_t gemm_partial_elems_upto(int dtype, int M_max, int N, int K, bool paired, bool fused);
 
 // ---- elementwise / small ------------------------------------------------------
 // h[r][:] = float(E[tok[r]][:]), r < rows.

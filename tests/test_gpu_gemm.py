@@ -32,7 +32,15 @@ SHAPES = [(1, 64, 64), (17, 100, 128), (33, 1000, 512), (100, 384, 4096), (129, 
           # paired few-row tiles with 512-byte rows per copy (K steps of 256), ragged N
           (21, 4100, 2048),
           # thousands of rows, ragged in M and N, ten K steps (the 256 x 256 tile)
-          (2600, 1100, 640)]
+          (2600, 1100, 640),
+          # 128 x 128 tiles: one to four K steps, ragged edges, one and two
+          # work-groups a CU, K split; the rows where the choice changes
+          (113, 130, 64), (129, 127, 128), (300, 200, 192), (771, 2048, 512), (513, 4100, 256), (200, 2048, 2048),
+          (640, 300, 3072), (1500, 1000, 448),
+          # 256 x 256 tiles in five LDS slots: one to five K steps
+          (5000, 2600, 64), (5100, 2570, 128), (4900, 2600, 320),
+          # few rows, short K: no split where a reduction would cost more
+          (64, 1536, 512), (21, 8192, 512)]
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
