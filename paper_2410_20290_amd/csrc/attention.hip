@@ -312,6 +312,21 @@ __device__ __forceinline__ int vslot(int k, int c) {
   else return c ^ ((k & 3) << 1);
 }
 
+// Sum of split partials: load(offset, x) reads NX values of a split, add(x)
+// accumulates them, in split order; the loads of U splits go out together
+// (one memory round trip per U splits).
+template <int U, int NX, typename T = float, typename Load, typename Add>
+__device__ __forceinline__ void sum_splits(int splits, int64_t stride, Load&& load, Add&& add) {
+  for (int s0 = 0; s0 < splits; s0 += U) {
+    T x[U][NX];
+#pragma unroll
+    for (int u = 0; u < U; ++u) load(min(s0 + u, splits - 1) * stride, x[u]);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (s0 + u < splits) add(x[u]);
+  }
+}
+
 // The K rows of keys [k0, k1) (at most 32) as A operand rows: key 16 t + l %
 // 16, dims 32 st + 8 (l / 16) .. + 8; keys past the end repeat the last.
 template <int HD>
@@ -420,20 +435,21 @@ decode_wave_kernel(const float* __restrict__ q, const bf16_t* __restrict__ kpre,
     const float* pv = pk + hkv * HD;
     const int64_t at = (((int64_t)row * hkv + h) * cap + lt - 1) * HD;
     for (int d = lane; d < HD / 2; d += 64) {
-      float k1v = 0.f, k2v = 0.f, v1 = 0.f, v2 = 0.f;
-      for (int sp = 0; sp < qsplits; ++sp) {
-        k1v += pk[sp * qs + d];
-        k2v += pk[sp * qs + HD / 2 + d];
-        v1 += pv[sp * qs + d];
-        v2 += pv[sp * qs + HD / 2 + d];
-      }
       const float2 c = rope[d];
+      float k1v = 0.f, k2v = 0.f, v1 = 0.f, v2 = 0.f;
+      sum_splits<4, 4>(qsplits, qs, [&](int64_t o, float(&x)[4]) {
+        x[0] = pk[o + d];
+        x[1] = pk[o + HD / 2 + d];
+        x[2] = pv[o + d];
+        x[3] = pv[o + HD / 2 + d];
+      }, [&](const float(&x)[4]) {
+        k1v += x[0]; k2v += x[1]; v1 += x[2]; v2 += x[3];
+      });
       ktail[at + d] = f32_to_bf16(k1v * c.x - k2v * c.y);
       ktail[at + HD / 2 + d] = f32_to_bf16(k2v * c.x + k1v * c.y);
       vtail[at + d] = f32_to_bf16(v1);
       vtail[at + HD / 2 + d] = f32_to_bf16(v2);
     }
-    vm_wait<0>();
   }
 
   // Q^T fragments (B operand): lane holds Q[query fr][32 s + 8 fg .. + 8],
@@ -452,18 +468,15 @@ decode_wave_kernel(const float* __restrict__ q, const bf16_t* __restrict__ kpre,
       const int64_t qs = (int64_t)gridDim.z * qkv_dim;
       const float* pq = qpart + (int64_t)row * qkv_dim + qh * HD + 8 * fg;
       if (qvalid)
-        for (int sp = 0; sp < qsplits; ++sp) {
+        sum_splits<HD == 64 ? 4 : 2, 2 * KS, f32x4>(qsplits, qs, [&](int64_t o, f32x4(&v)[2 * KS]) {
 #pragma unroll
-          for (int st = 0; st < KS; ++st) {
-            const f32x4 a = *reinterpret_cast<const f32x4*>(pq + sp * qs + 32 * st);
-            const f32x4 b = *reinterpret_cast<const f32x4*>(pq + sp * qs + 32 * st + 4);
+          for (int i = 0; i < 2 * KS; ++i) v[i] = *reinterpret_cast<const f32x4*>(pq + o + 32 * (i / 2) + 4 * (i % 2));
+        }, [&](const f32x4(&v)[2 * KS]) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              x[st][e] += a[e];
-              x[st][4 + e] += b[e];
-            }
-          }
-        }
+          for (int i = 0; i < 2 * KS; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[i / 2][4 * (i % 2) + e] += v[i][e];
+        });
       float* qo = qout && split == 0 && wave == 0 && qvalid ? qout + ((int64_t)row * hq + qh) * HD : nullptr;
 #pragma unroll
       for (int st = 0; st < KS / 2; ++st)
@@ -575,6 +588,7 @@ decode_wave_kernel(const float* __restrict__ q, const bf16_t* __restrict__ kpre,
   };
   const std::integral_constant<int, INFLIGHT> next{};
   if (nb > 0) {
+    if (writer) vm_wait<0>();   // the newest key's row is in memory before it is read
     if (!early) {
       load_k(0, ka);
       copy_v(0, 0);
@@ -701,20 +715,21 @@ decode_group_kernel(const float* __restrict__ q, const bf16_t* __restrict__ kpre
     const float* pv = pk + hkv * HD;
     const int64_t at = (((int64_t)row * hkv + h) * cap + lt - 1) * HD;
     for (int d = lane; d < HD / 2; d += 64) {
-      float k1v = 0.f, k2v = 0.f, v1 = 0.f, v2 = 0.f;
-      for (int sp = 0; sp < qsplits; ++sp) {
-        k1v += pk[sp * qs + d];
-        k2v += pk[sp * qs + HD / 2 + d];
-        v1 += pv[sp * qs + d];
-        v2 += pv[sp * qs + HD / 2 + d];
-      }
       const float2 c = rope[d];
+      float k1v = 0.f, k2v = 0.f, v1 = 0.f, v2 = 0.f;
+      sum_splits<4, 4>(qsplits, qs, [&](int64_t o, float(&x)[4]) {
+        x[0] = pk[o + d];
+        x[1] = pk[o + HD / 2 + d];
+        x[2] = pv[o + d];
+        x[3] = pv[o + HD / 2 + d];
+      }, [&](const float(&x)[4]) {
+        k1v += x[0]; k2v += x[1]; v1 += x[2]; v2 += x[3];
+      });
       ktail[at + d] = f32_to_bf16(k1v * c.x - k2v * c.y);
       ktail[at + HD / 2 + d] = f32_to_bf16(k2v * c.x + k1v * c.y);
       vtail[at + d] = f32_to_bf16(v1);
       vtail[at + HD / 2 + d] = f32_to_bf16(v2);
     }
-    vm_wait<0>();
   }
 
   // Q^T (B operand): column fr = row grp R + fr / G, query head h G + fr % G
@@ -732,18 +747,15 @@ decode_group_kernel(const float* __restrict__ q, const bf16_t* __restrict__ kpre
       const int64_t qs = (int64_t)rows * qkv_dim;
       const float* pq = qpart + (int64_t)qr * qkv_dim + qh * HD + 8 * fg;
       if (qvalid)
-        for (int sp = 0; sp < qsplits; ++sp) {
+        sum_splits<HD == 64 ? 4 : 2, 2 * KS, f32x4>(qsplits, qs, [&](int64_t o, f32x4(&v)[2 * KS]) {
 #pragma unroll
-          for (int st = 0; st < KS; ++st) {
-            const f32x4 a = *reinterpret_cast<const f32x4*>(pq + sp * qs + 32 * st);
-            const f32x4 b = *reinterpret_cast<const f32x4*>(pq + sp * qs + 32 * st + 4);
+          for (int i = 0; i < 2 * KS; ++i) v[i] = *reinterpret_cast<const f32x4*>(pq + o + 32 * (i / 2) + 4 * (i % 2));
+        }, [&](const f32x4(&v)[2 * KS]) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              x[st][e] += a[e];
-              x[st][4 + e] += b[e];
-            }
-          }
-        }
+          for (int i = 0; i < 2 * KS; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[i / 2][4 * (i % 2) + e] += v[i][e];
+        });
 #pragma unroll
       for (int st = 0; st < KS / 2; ++st)
 #pragma unroll
@@ -862,6 +874,7 @@ decode_group_kernel(const float* __restrict__ q, const bf16_t* __restrict__ kpre
     compute(key0(b), keyend(b), b >= np, kr, bufc);
     __builtin_amdgcn_sched_barrier(0);
   };
+  if (writer) vm_wait<0>();   // the newest key's row is in memory before it is read
   if (nb > 0) {
     uint4 ka[2][KS], kb[2][KS];
     fetch(0, ka, 0);

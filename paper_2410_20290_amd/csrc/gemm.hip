@@ -1734,7 +1734,7 @@ GemmPlan gemm_plan(int dtype, int M, int N, int K, bool paired, bool fused) {
     const int64_t tiles = (int64_t)((M + p.stream - 1) / p.stream) * ((N + p.stream_bn - 1) / p.stream_bn);
     double t_best = 0.0;
     for (int splits = 1; splits == 1 || (tiles * splits <= 256 && K % (splits * 128) == 0); splits *= 2) {
-      double t = 0.7 * (K / 128 / splits);
+      double t = 0.7 * (K / 128 / splits) + 0.25 * splits;   // (a consumer reads every split)
       if (!fused && splits > 1) t += 5.0 + 0.33e-6 * 4.0 * (splits * (paired ? 2 : 1) + 1) * p.stream * N;
       if (splits == 1 || t < t_best) {
         p.splits = splits;
