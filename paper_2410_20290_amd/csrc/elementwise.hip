@@ -215,11 +215,11 @@ void rope_scatter(int dtype, const float* qkv, int rows, int lr, int hq, int hkv
 // walked the row by single elements, twice).
 template <typename T, bool VEC>
 __global__ void __launch_bounds__(256)
-embed_norm_kernel(const T* __restrict__ E, int d, const int32_t* __restrict__ tok, const T* __restrict__ g,
+embed_norm_kernel(const T* __restrict__ E, int d, const int32_t* __restrict__ tok, int tok_ld, const T* __restrict__ g,
                   float eps, float* __restrict__ h, T* __restrict__ xn) {
   __shared__ float red[4];
   const int r = blockIdx.x;
-  const T* src = E + (int64_t)tok[r] * d;
+  const T* src = E + (int64_t)tok[(int64_t)r * tok_ld] * d;
   float* hr = h + (int64_t)r * d;
   T* o = xn + (int64_t)r * d;
   float ss = 0.f;
@@ -255,12 +255,12 @@ embed_norm_kernel(const T* __restrict__ E, int d, const int32_t* __restrict__ to
   }
 }
 
-void embed_norm(int dtype, const void* E, int d, const int32_t* tok, int rows, const void* g, float eps,
+void embed_norm(int dtype, const void* E, int d, const int32_t* tok, int tok_ld, int rows, const void* g, float eps,
                 float* h, void* xn, hipStream_t s) {
   if (rows <= 0) return;
   const bool vec = rows_vec(E, h, d) && rows_vec(g, (const float*)xn, d) && d <= 4096;
 #define SR_EMBED_NORM(T, V)                                                                                   \
-  SR_LAUNCH((embed_norm_kernel<T, V>), dim3(rows), dim3(256), 0, s, (const T*)E, d, tok, (const T*)g, eps, h, \
+  SR_LAUNCH((embed_norm_kernel<T, V>), dim3(rows), dim3(256), 0, s, (const T*)E, d, tok, tok_ld, (const T*)g, eps, h, \
             (T*)xn)
   if (dtype == SR_BF16 && vec) SR_EMBED_NORM(bf16_t, true);
   else if (dtype == SR_BF16) SR_EMBED_NORM(bf16_t, false);

@@ -21,7 +21,7 @@ namespace sr {
 struct EpiArgs {
   int mode;       // GemmEpi
   void* out;      // destination (type per mode)
-  int ldo;        // leading dimension of out (elements)
+  int64_t ldo;    // leading dimension of out (elements)
   int out_bf16;   // for EPI_STORE and EPI_SWIGLU: 1 = bf16 out, 0 = fp32 out
 };
 

@@ -393,7 +393,7 @@ static void timed(const Ctx& c, int cls, double bytes, double flops, F&& launch)
 // Projection launch.  decode: a generator decode projection (classed by
 // whether its rows make it MFMA- or weight-bound), else reward/prefill.
 static int run_gemm(const Ctx& c, bool decode, int dtype, const void* A, int lda, const void* B, int ldb,
-                    int M, int N, int K, int epi, void* out, int ldo, int out_bf16, bool paired = false,
+                    int M, int N, int K, int epi, void* out, int64_t ldo, int out_bf16, bool paired = false,
                     int64_t pair_off = 0) {
   GemmArgs g;
   g.dtype = dtype; g.A = A; g.lda = lda; g.B = B; g.ldb = ldb; g.pair_off = pair_off;
@@ -513,17 +513,18 @@ static void reward_rows(const Ctx& c, const Model& R, const int32_t* cand, const
   }
 }
 
-// One decode step for `rows` rows: feed st.tok (response token t = step-1 at
-// position P + step - 1) through the generator, append its K/V to the tail
-// pool at index step-1 and leave the logits of the next token in L.logits.
-static void decode_step(const Ctx& c, const Model& G, const State& st, int rows, int step, void* pool,
-                        int64_t pool_block, int cap) {
+// One decode step for `rows` rows: feed tok[r * tok_ld] (response token t =
+// step-1 at position P + step - 1) through the generator, append its K/V to
+// the tail pool at index step-1 and write the logits of the next token to
+// rows of `logits` (ld floats apart).
+static void decode_step(const Ctx& c, const Model& G, const int32_t* tok, int tok_ld, int rows, int step, void* pool,
+                        int64_t pool_block, int cap, float* logits, int64_t ld) {
   const Dims& m = G.m;
   Layout& L = *c.L;
   const Plan& pl = *c.pl;
   const int bf = m.dtype == SR_BF16;
   run_other(c, (double)rows * m.d * (4 + m.es), [&] {
-    embed_norm(m.dtype, G.w->embed, m.d, st.tok, rows, G.attn_norm(0), m.eps, L.h, L.xn, c.s);
+    embed_norm(m.dtype, G.w->embed, m.d, tok, tok_ld, rows, G.attn_norm(0), m.eps, L.h, L.xn, c.s);
   });
   const size_t pre_lay = (size_t)2 * m.hkv * pl.P * m.hd * m.es;
   for (int l = 0; l < m.nl; ++l) {
@@ -568,7 +569,7 @@ static void decode_step(const Ctx& c, const Model& G, const State& st, int rows,
       add_norm(m.dtype, L.gpart, sp, rows, m.d, L.h, gnext, m.eps, L.xn, c.s);
     });
   }
-  run_gemm(c, true, m.dtype, L.xn, m.d, G.w->head, m.d, rows, m.V, m.d, EPI_STORE, L.logits, m.V, 0);
+  run_gemm(c, true, m.dtype, L.xn, m.d, G.w->head, m.d, rows, m.V, m.d, EPI_STORE, logits, ld, 0);
 }
 
 // Logits of the last prompt token into logits row 0 (after prompt_prefill,
@@ -605,9 +606,10 @@ __global__ void lens_kernel(const int32_t* len, int n, int32_t* cand_len, const 
   if (i < n) cand_len[cand[i]] = len[i];
 }
 
-__global__ void column_kernel(const int32_t* tokens, int ld, int col, int rows, int32_t* out) {
-  int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r < rows) out[r] = tokens[(int64_t)r * ld + col];
+// dst[r * ld + i] = src[i] for every row r (grid (blocks, rows)).
+__global__ void __launch_bounds__(256)
+broadcast_row_kernel(const float* __restrict__ src, int n, int64_t ld, float* __restrict__ dst) {
+  for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) dst[blockIdx.y * ld + i] = src[i];
 }
 
 struct Timer {
@@ -739,7 +741,7 @@ static void generate(const sr_model* gen, const sr_model* rm, const int32_t* pro
     for (; step < D; ++step) {
       prof.active = every > 0 && step % every == 0;
       const State& st = L.st[cur];
-      if (step > 0) decode_step(c, G, st, b, step, L.pool[cur], pl.S[cur] * gd.hkv * gd.hd, cap);
+      if (step > 0) decode_step(c, G, st.tok, 1, b, step, L.pool[cur], pl.S[cur] * gd.hkv * gd.hd, cap, L.logits, gd.V);
       for (int w = 0; w < (int)watch_row.size(); ++w)
         if (watch_row[w] >= 0)
           copy_d2h(tr->watch_logits + ((size_t)w * Lmax + step) * gd.V,
@@ -981,18 +983,15 @@ static void teacher_forced(const sr_model* gen, const sr_model* rm, const int32_
   prompt_prefill(c, G, L.rope_g, L.gpre);
   prompt_logits(c, G);
   const size_t V = gd.V;
-  for (int r = 0; r < rows; ++r)
-    SR_HIP(hipMemcpyAsync(logits_out + (size_t)r * len * V, L.logits, V * sizeof(float),
-                          hipMemcpyDeviceToDevice, s));
-  State st = L.st[0];
-  for (int t = 1; t < len; ++t) {
-    SR_LAUNCH(column_kernel, dim3((rows + 255) / 256), dim3(256), 0, s, tokens, len, t - 1, rows,
-                       st.tok);
-    SR_CHECK_LAUNCH();
-    decode_step(c, G, st, rows, t, L.pool[0], pl.S[0] * gd.hkv * gd.hd, len);
-    SR_HIP(hipMemcpy2DAsync(logits_out + (size_t)t * V, (size_t)len * V * sizeof(float), L.logits,
-                            V * sizeof(float), V * sizeof(float), rows, hipMemcpyDeviceToDevice, s));
-  }
+  const int64_t ld = (int64_t)len * V;
+  SR_LAUNCH(broadcast_row_kernel, dim3(std::min((gd.V + 255) / 256, 64), rows), dim3(256), 0, s, L.logits, gd.V, ld,
+            logits_out);
+  SR_CHECK_LAUNCH();
+  // every step reads its column of `tokens` and writes its slice of
+  // logits_out in place
+  for (int t = 1; t < len; ++t)
+    decode_step(c, G, tokens + t - 1, len, rows, t, L.pool[0], pl.S[0] * gd.hkv * gd.hd, len, logits_out + (size_t)t * V,
+                ld);
   SR_HIP(hipStreamSynchronize(s));
 }
 

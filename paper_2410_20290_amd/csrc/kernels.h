@@ -24,7 +24,7 @@ struct GemmArgs {
                          // (fp32 split partials [splits][M][N] left in `partial` for a
                          // fused consumer; gemm() returns the split count); paired: store
   void* out;
-  int ldo;
+  int64_t ldo;
   int out_bf16;          // EPI_STORE / paired: 1 = bf16 out, 0 = fp32 out
 };
 enum GemmKind {
@@ -72,8 +72,8 @@ void score_head(int dtype, const float* h, int d, int lr, int t0, const int32_t*
 void gather_tokens(const int32_t* store, int ld, const int32_t* cand, const int32_t* len, int rows,
                    int t0, int lr, int32_t* tokens, hipStream_t s);
 void philox_fill(uint64_t seed, const uint32_t* ctr, int n, uint32_t* out, hipStream_t s);
-// h[r] = E[tok[r]] (fp32); xn[r] = RMSNorm(h[r]) * g (model dtype).
-void embed_norm(int dtype, const void* E, int d, const int32_t* tok, int rows, const void* g, float eps,
+// h[r] = E[tok[r * tok_ld]] (fp32); xn[r] = RMSNorm(h[r]) * g (model dtype).
+void embed_norm(int dtype, const void* E, int d, const int32_t* tok, int tok_ld, int rows, const void* g, float eps,
                 float* h, void* xn, hipStream_t s);
 // h[r] += sum_s part[s][r]; xn[r] = RMSNorm(h[r]) * g (model dtype); d columns.
 void add_norm(int dtype, const float* part, int splits, int rows, int d, float* h, const void* g, float eps,
