@@ -1665,7 +1665,11 @@ static int stream_tile_rows(int M) { return M <= 32 ? 32 : (M <= 64 ? 64 : (M <=
 // 128-column tiles run one work-group a CU; of the 128 x 128 tiles two share a
 // CU, at 0.95 us a step together against 0.62 us alone.  Rows are counted in
 // whole 128s, so the choice is the same within each.
-static double tile_cost(GemmKind kind, int M, int N, int K, bool paired, int splits) {
+// Partials that the next kernel sums itself (`fused`) cost that kernel their
+// bytes and nothing else: 512 rows of the 8B QKV projection take 33 us in two
+// splits of 256 x 128 tiles and 52 us unsplit in 128 x 128 ones, where a
+// reduction launch would add 17 us to the former.
+static double tile_cost(GemmKind kind, int M, int N, int K, bool paired, int splits, bool fused) {
   const int bm = kind == GEMM_TILE128 ? 128 : 256;
   const int bn = (kind == GEMM_TILE128 || kind == GEMM_DMA3 ? 128 : 256) / (paired ? 2 : 1);
   const int64_t groups = (int64_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn) * splits;
@@ -1682,11 +1686,14 @@ static double tile_cost(GemmKind kind, int M, int N, int K, bool paired, int spl
     t = 3.2 + one * (1.07 * steps + 8.8);
   }
   const double rows = (M + 127) / 128 * 128.0;
-  if (splits > 1) t += 5.0 + 0.33e-6 * 4.0 * (splits * (paired ? 2 : 1) + 1) * rows * N;
+  if (splits > 1) {
+    t += fused ? 0.33e-6 * 4.0 * (splits - 1) * rows * N
+               : 5.0 + 0.33e-6 * 4.0 * (splits * (paired ? 2 : 1) + 1) * rows * N;
+  }
   return t;
 }
 
-static GemmPlan tile_plan(int M, int N, int K, bool paired) {
+static GemmPlan tile_plan(int M, int N, int K, bool paired, bool fused) {
   GemmPlan best{GEMM_REG, 1, 0, 0};
   if (K % 64 != 0) return best;
   double t_best = 0.0;
@@ -1697,7 +1704,7 @@ static GemmPlan tile_plan(int M, int N, int K, bool paired) {
       if (K % (splits * 64) != 0 || (splits > 1 && K / splits < 512)) break;
       // (bounds the partials: beyond, a split would gain a few percent at most)
       if (splits > 1 && !(tiles128 * splits < 1024 || (M > 1024 && tiles256 * splits <= 256))) break;
-      const double t = tile_cost(kind, M, N, K, paired, splits);
+      const double t = tile_cost(kind, M, N, K, paired, splits, fused);
       if (best.kind == GEMM_REG || t < t_best) {
         best.kind = kind;
         best.splits = splits;
@@ -1743,7 +1750,7 @@ GemmPlan gemm_plan(int dtype, int M, int N, int K, bool paired, bool fused) {
     }
     return p;
   }
-  if (M > 64) return tile_plan(M, N, K, paired);
+  if (M > 64) return tile_plan(M, N, K, paired, fused);
   // up to 64 rows with K not a multiple of 128: register-staged tiles, K split
   // while the grid alone cannot fill 256 CUs twice over; each split keeps at
   // least 512 of K and a multiple of 64
