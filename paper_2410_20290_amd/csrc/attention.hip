@@ -21,6 +21,7 @@
 // head_dim 64/128), or a block of queries on the vector ALU with K/V staged
 // in LDS as fp32.
 #include <algorithm>
+#include <cfloat>
 #include <mutex>
 #include <type_traits>
 
@@ -1635,7 +1636,10 @@ prefill_attn_mfma_kernel(const float* __restrict__ q, const bf16_t* __restrict__
   for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
     for (int e = 0; e < 16; ++e) o[dt][e] = 0.f;
-  float m = -INFINITY, l = 0.f;
+  // The running maximum starts at the lowest finite score: while a column has
+  // seen only scores of -inf (an infinite key, products that overflow), their
+  // probabilities are exp2(-inf) = 0, where -inf - -inf would be NaN.
+  float m = -FLT_MAX, l = 0.f;
 
   auto zero = [](f32x16& sc) {
 #pragma unroll
@@ -1697,7 +1701,7 @@ prefill_attn_mfma_kernel(const float* __restrict__ q, const bf16_t* __restrict__
     mt = fmaxf(mt, other_half(mt));
     if (__any(mt > m + kLazyMax)) {
       const float mn = fmaxf(m, mt);
-      const float corr = mn == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m - mn);
+      const float corr = __builtin_amdgcn_exp2f(m - mn);
       l *= corr;
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt) o[dt] *= corr;

@@ -189,3 +189,52 @@ def test_prefill_attention_after_nans(hd, hq, hkv, rows, P, t0, lr):
         qf[P + t0:] = q[r].double().cpu().numpy()
         ref = causal_attention(qf, k, v, hkv)[P + t0:]
         assert np.abs(got[r] - ref).max() <= 1e-2 * np.abs(ref).max()
+
+
+def dev_attention64(torch, q, k, v):
+    """float64 attention on the device: q [..., G, hd] against k, v [..., T, hd]."""
+    s = torch.matmul(q.double(), k.double().transpose(-1, -2).contiguous()) / q.shape[-1] ** 0.5
+    return torch.matmul(torch.softmax(s, -1), v.double())
+
+
+@pytest.mark.parametrize("hd,hq,hkv", [(128, 32, 8), (64, 8, 8), (64, 16, 8), (128, 64, 8)])
+@pytest.mark.parametrize("blind", [33, 64, 100])
+@pytest.mark.parametrize("how", ["inf", "overflow"])
+def test_attention_first_scores_minus_infinity(hd, hq, hkv, blind, how):
+    """The first `blind` keys score -inf for every query (infinite key
+    components, or products that overflow), all later ones are finite: those
+    keys weigh 0 and the others form the softmax, in prefill and in both
+    decode forms, also where a wave's first blocks hold no finite score."""
+    torch, sr = need_gpu()
+    say(f"-inf scores hd={hd} hq={hq} hkv={hkv} blind={blind} {how}")
+    bf, rows, P, lr, lt, G = torch.bfloat16, 2, 130, 40, 70, hq // hkv
+    g = torch.Generator(device="cuda").manual_seed(hd + hq + blind)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda")
+
+    def queries(*s):
+        q = rnd(*s)
+        q[..., :16] = 2.0   # (16 products of -3e38 x 2 / sqrt(hd) overflow)
+        return q
+    kp, vp = rnd(hkv, P, hd).to(bf), rnd(hkv, P, hd).to(bf)
+    kp[:, :blind, :16] = -float("inf") if how == "inf" else -3.0e38
+    ko, vo = rnd(rows, hkv, lr, hd).to(bf), rnd(rows, hkv, lr, hd).to(bf)
+    q = queries(rows, lr, hq, hd)
+    out = torch.empty((rows, lr, hq * hd), dtype=bf, device="cuda")
+    sr.prefill_attention(q, kp, vp, ko, vo, 0, out)
+    got = out.double().view(rows, lr, hkv, G, hd)
+    assert bool(torch.isfinite(got).all())
+    for r in range(rows):
+        for t in range(lr):
+            k, v = (torch.cat([a[:, blind:], b[r][:, : t + 1]], 1) for a, b in ((kp, ko), (vp, vo)))
+            ref = dev_attention64(torch, q[r, t].view(hkv, G, hd), k, v)
+            assert float((got[r, t] - ref).abs().max()) <= 1e-2 * float(ref.abs().max())
+    for nrow in (5, 70):   # one row a work-group, row groups
+        kt, vt = rnd(nrow, hkv, lt, hd).to(bf), rnd(nrow, hkv, lt, hd).to(bf)
+        qd = queries(nrow, hq, hd)
+        o = torch.empty((nrow, hq * hd), dtype=bf, device="cuda")
+        sr.decode_attention(qd, kp, vp, kt, vt, lt, o)
+        k, v = (torch.cat([a[:, blind:].expand(nrow, -1, -1, -1), b], 2) for a, b in ((kp, kt), (vp, vt)))
+        ref = dev_attention64(torch, qd.view(nrow, hkv, G, hd), k, v)
+        dec = o.double().view(nrow, hkv, G, hd)
+        assert bool(torch.isfinite(dec).all())
+        assert float((dec - ref).abs().max()) <= 1e-2 * float(ref.abs().max())
