@@ -32,10 +32,6 @@ namespace sr {
 
 constexpr float kLog2e = 1.4426950408889634f;
 
-// Online softmax: log2 of the growth of the scores that moves the reference
-// maximum of a column.
-constexpr float kLazyMax = 8.0f;
-
 __device__ __forceinline__ float exp2_or_zero(float x) { return x == -INFINITY ? 0.f : exp2f(x); }
 
 // Work-group barrier after this wave's LDS reads and writes complete; vector
@@ -542,9 +538,11 @@ decode_wave_kernel(const float* __restrict__ q, const bf16_t* __restrict__ kpre,
     for (int i = 1; i < 8; ++i) mt = fmaxf(mt, sv[i]);
     mt = fmaxf(mt, __shfl_xor(mt, 16, 64));
     mt = fmaxf(mt, __shfl_xor(mt, 32, 64));
-    // the reference maximum moves (and the accumulators are rescaled) only
-    // when some column exceeds it by 2^8
-    if (__any(mt > m + kLazyMax)) {
+    // The accumulators are rescaled only when some column's maximum grows (by
+    // exactly 1 elsewhere).  Probabilities are relative to the exact maximum, so
+    // the largest, 1, loses nothing in bf16: relative to a maximum up to 2^8
+    // stale the output was 3-5 % further off.
+    if (__any(mt > m)) {
       const float mn = fmaxf(m, mt);
       const float corr = mn == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m - mn);
       l *= corr;
@@ -819,9 +817,11 @@ decode_group_kernel(const float* __restrict__ q, const bf16_t* __restrict__ kpre
     for (int i = 1; i < 8; ++i) mt = fmaxf(mt, sv[i]);
     mt = fmaxf(mt, __shfl_xor(mt, 16, 64));
     mt = fmaxf(mt, __shfl_xor(mt, 32, 64));
-    // the reference maximum moves (and the accumulators are rescaled) only
-    // when some column exceeds it by 2^8
-    if (__any(mt > m + kLazyMax)) {
+    // The accumulators are rescaled only when some column's maximum grows (by
+    // exactly 1 elsewhere).  Probabilities are relative to the exact maximum, so
+    // the largest, 1, loses nothing in bf16: relative to a maximum up to 2^8
+    // stale the output was 3-5 % further off.
+    if (__any(mt > m)) {
       const float mn = fmaxf(m, mt);
       const float corr = mn == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m - mn);
       l *= corr;
@@ -1526,17 +1526,18 @@ prefill_attn_kernel(const float* __restrict__ q, const T* __restrict__ kpre, con
 // probabilities of these; 16-byte chunks sit XOR-swizzled in the LDS rows (K:
 // the fragment reads of eight neighbouring keys, V: the transpose reads of a
 // half wave, on distinct banks).  Queries and outputs pass through LDS too, so
-// that memory sees whole rows.  Online softmax in base 2; the running maximum
-// a column is scaled by moves only when 32 keys exceed it by more than 2^8 in
-// some column, so most leave the 64 accumulators alone (probabilities, sum
-// and output stay fp32 multiples of the same scale).
+// that memory sees whole rows.  Online softmax in base 2 relative to each
+// column's exact maximum.  (A maximum up to 2^8 stale spares most rescalings of
+// the 64 accumulators, 844 -> 795 us at the longest case below, but puts the
+// output 5 % further off: the largest probability is then rounded to bf16
+// where it would be exactly 1.)
 // Four waves and 32-key tiles, two work-groups a CU (eight waves and 64-key
 // tiles with 8 query heads a KV head): eight waves in one work-group were
 // 5-17 % slower on short responses and at head_dim 64.
 // Against 16-query waves with tiles staged through registers, head_dim 128:
-// 103 rows x 32 heads x 507 queries after 384 keys 1136 -> 798 us, 512 rows
-// of 128 queries after 256 keys 833 -> 632 us (3 TB/s of queries, outputs and
-// keys), one prompt of 256 15.5 -> 11.4 us.  What is left is issue: VALU
+// 103 rows x 32 heads x 507 queries after 384 keys 1198 -> 856 us, 512 rows
+// of 128 queries after 256 keys 873 -> 685 us (2.8 TB/s of queries, outputs and
+// keys), one prompt of 256 15.4 -> 12.0 us.  What is left is issue: VALU
 // (16 exponentials of 32 keys take as long as half their MFMAs), MFMA and LDS
 // waits overlap only across the two waves of a SIMD.
 constexpr int PF_NST = 4;            // stages
@@ -1699,7 +1700,7 @@ prefill_attn_mfma_kernel(const float* __restrict__ q, const bf16_t* __restrict__
 #pragma unroll
     for (int e = 1; e < 16; ++e) mt = fmaxf(mt, sc[e]);
     mt = fmaxf(mt, other_half(mt));
-    if (__any(mt > m + kLazyMax)) {
+    if (__any(mt > m)) {
       const float mn = fmaxf(m, mt);
       const float corr = __builtin_amdgcn_exp2f(m - mn);
       l *= corr;
