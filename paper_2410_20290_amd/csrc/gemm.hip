@@ -1648,8 +1648,8 @@ size_t gemm_partial_elems_upto(int dtype, int M_max, int N, int K, bool paired, 
 //  - up to kStreamMaxRows rows the LDS-DMA streaming kernel (weights read
 //    once, one work-group per CU);
 //  - above, the tile kernel and K split that tile_plan expects to be fastest;
-//  - the register-staged tiles when an operand is too large for 32-bit buffer
-//    offsets.
+//  - the register-staged tiles where the operands do not suit LDS DMA
+//    (dma_fits).
 constexpr int kStreamMaxRows = 128;
 constexpr int kWringMaxRows = 512;
 constexpr int kBigTileMinRows = 1024;
@@ -1763,14 +1763,18 @@ GemmPlan gemm_plan(int dtype, int M, int N, int K, bool paired, bool fused) {
   p.splits = splits;
   return p;
 }
-// The LDS-DMA kernels address their operands with 32-bit byte offsets from
-// the K base of the split; the tiled ones pass them to buffer loads as signed
-// 32-bit vector offsets, so there they stay below 2 GiB (larger operands take
-// the register-staged kernels).
-static bool dma_offsets_fit(const GemmArgs& g, int bits = 32) {
+// Whether the LDS-DMA kernels take the operands.  They copy 16 bytes a lane
+// straight into LDS, so every row starts on a 16-byte boundary; and they
+// address with 32-bit byte offsets from the K base of the split, which the
+// tiled ones pass to buffer loads as signed 32-bit vector offsets, so there an
+// operand stays below 2 GiB.  Others take the register-staged kernels, whose
+// global loads have neither bound.
+static bool dma_fits(const GemmArgs& g, int bits) {
   const int64_t a = ((int64_t)(g.M - 1) * g.lda + g.K) * 2;
   const int64_t b = ((g.paired ? g.pair_off : 0) + (int64_t)(g.N - 1) * g.ldb + g.K) * 2;
-  return a < (1LL << bits) && b < (1LL << bits) && g.pair_off >= 0;
+  const bool aligned = ((reinterpret_cast<uintptr_t>(g.A) | reinterpret_cast<uintptr_t>(g.B)) & 15) == 0 &&
+                       g.lda % 8 == 0 && g.ldb % 8 == 0 && (!g.paired || g.pair_off % 8 == 0);
+  return aligned && a < (1LL << bits) && b < (1LL << bits) && g.pair_off >= 0;
 }
 
 int gemm(const GemmArgs& g, float* partial, size_t partial_cap, hipStream_t s) {
@@ -1821,7 +1825,7 @@ int gemm(const GemmArgs& g, float* partial, size_t partial_cap, hipStream_t s) {
                "GEMM partial buffer too small");
     part = partial;
   }
-  if (plan.kind == GEMM_STREAM && dma_offsets_fit(g)) {
+  if (plan.kind == GEMM_STREAM && dma_fits(g, 32)) {
     dim3 grid = tile_grid((g.M + plan.stream - 1) / plan.stream, (g.N + plan.stream_bn - 1) / plan.stream_bn, splits);
 #define SR_STREAM(BM, BN, WGM, WGN, NST, P, BK, ROT)                                                    \
   SR_LAUNCH((gemm_stream_kernel<BM, BN, WGM, WGN, NST, P, BK>), grid, dim3(256), 0, s,           \
@@ -1860,7 +1864,7 @@ int gemm(const GemmArgs& g, float* partial, size_t partial_cap, hipStream_t s) {
 #undef SR_RING
 #undef SR_STREAM
     SR_CHECK_LAUNCH();
-  } else if (plan.kind >= GEMM_TILE128 && dma_offsets_fit(g, 31)) {
+  } else if (plan.kind >= GEMM_TILE128 && dma_fits(g, 31)) {
     const int bm = plan.kind == GEMM_TILE128 ? 128 : 256;
     const int bn = (plan.kind == GEMM_TILE128 || plan.kind == GEMM_DMA3 ? 128 : 256) / (g.paired ? 2 : 1);
     dim3 grid = tile_grid((g.M + bm - 1) / bm, (g.N + bn - 1) / bn, splits);

@@ -131,3 +131,32 @@ def test_projection_f32_unaligned(M, N, K, mode):
         ref = x64 @ w64.T + (init if mode == 1 else 0)
     bound = (K + 2) * 2.0 ** -24 * max(1.0, float((np.abs(x64) @ np.abs(w64.reshape(-1, K)).T).max())) ** 2
     assert np.abs(out.cpu().numpy() - ref).max() <= bound
+
+
+@pytest.mark.parametrize("mode", [1, 2])
+@pytest.mark.parametrize("which", ["x", "w"])
+@pytest.mark.parametrize("M,N,K", [(20, 100, 256), (50, 100, 256), (70, 200, 192), (100, 200, 256), (600, 300, 1024),
+                                   (1100, 300, 256)])
+def test_projection_bf16_unaligned(M, N, K, which, mode):
+    """bf16 operands that start on a 2-byte boundary: no 16-byte copy into LDS
+    takes them, the register-staged tiles do, at every row count that has a
+    streaming or an LDS-DMA tile plan."""
+    torch, sr = need_gpu()
+    say(f"projection bf16 unaligned {which} mode={mode} M={M} N={N} K={K}")
+    g = torch.Generator(device="cuda").manual_seed(M + N + K + mode)
+
+    def operand(shape, std, odd):
+        t = torch.empty(int(np.prod(shape)) + 8, dtype=torch.bfloat16, device="cuda").normal_(0, std, generator=g)
+        return t[odd:odd + int(np.prod(shape))].view(shape)
+    x = operand((M, K), 1.0, int(which == "x"))
+    w = operand((2, N, K) if mode == 2 else (N, K), 0.05, int(which == "w"))
+    x64, w64 = x.double(), w.double()
+    if mode == 2:
+        ga, up = x64 @ w64[0].T, x64 @ w64[1].T
+        ref, out = ga / (1 + torch.exp(-ga)) * up, torch.zeros((M, N), dtype=torch.bfloat16, device="cuda")
+    else:
+        out = torch.randn((M, N), generator=g, device="cuda")
+        ref = x64 @ w64.T + out.double()
+    sr.projection(x, w, mode, out)
+    torch.cuda.synchronize()
+    assert float((out.double() - ref).abs().max()) <= (1e-2 if mode == 2 else 1e-4) * float(ref.abs().max())
