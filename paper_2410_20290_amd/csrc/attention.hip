@@ -1854,7 +1854,14 @@ static void launch_prefill_mfma(const PrefillAttnArgs& a, hipStream_t s) {
 
 void prefill_attn(const PrefillAttnArgs& a, hipStream_t s) {
   if (a.rows <= 0 || a.lr <= 0) return;
-  if (a.dtype == SR_BF16 && a.hd == 128) {
+  // The matrix-core kernel copies keys and values 16 bytes a lane straight into
+  // LDS; rows off a 16-byte boundary take the vector kernel, whose global loads
+  // accept any address.
+  const bool mfma = a.dtype == SR_BF16 &&
+                    ((reinterpret_cast<uintptr_t>(a.kown) | reinterpret_cast<uintptr_t>(a.vown) |
+                      (a.P > 0 ? reinterpret_cast<uintptr_t>(a.kpre) | reinterpret_cast<uintptr_t>(a.vpre) : 0)) &
+                     15) == 0;
+  if (mfma && a.hd == 128) {
     switch (a.hq / a.hkv) {
       case 1: launch_prefill_mfma<128, 1>(a, s); return;
       case 2: launch_prefill_mfma<128, 2>(a, s); return;
@@ -1863,7 +1870,7 @@ void prefill_attn(const PrefillAttnArgs& a, hipStream_t s) {
       default: break;
     }
   }
-  if (a.dtype == SR_BF16 && a.hd == 64) {
+  if (mfma && a.hd == 64) {
     switch (a.hq / a.hkv) {
       case 1: launch_prefill_mfma<64, 1>(a, s); return;
       case 2: launch_prefill_mfma<64, 2>(a, s); return;

@@ -302,3 +302,32 @@ def test_prefill_attention_error(hd, hq, hkv, rows, P, t0, lr):
     by_head = lambda x: x.view(rows, lr, hkv, G, hd).permute(0, 2, 3, 1, 4)   # [rows][hkv][G][lr][hd]
     mask = torch.arange(T, device="cuda")[None, :] > (P + t0 + torch.arange(lr, device="cuda"))[:, None]
     no_further_off(torch, by_head(out), by_head(q), k.unsqueeze(2), v.unsqueeze(2), 1.0, mask)
+
+
+@pytest.mark.parametrize("odd", ["kpre", "vpre", "kown", "vown"])
+@pytest.mark.parametrize("hd,hq,hkv,P,t0,lr", [(128, 32, 8, 50, 20, 40), (64, 8, 8, 50, 0, 70), (64, 64, 8, 0, 9, 33)])
+def test_prefill_attention_unaligned(hd, hq, hkv, P, t0, lr, odd):
+    """Keys or values that start on a 2-byte boundary: no 16-byte copy into LDS
+    takes them, the vector kernel does."""
+    if P == 0 and odd in ("kpre", "vpre"):
+        pytest.skip("no prefix")
+    torch, sr = need_gpu()
+    say(f"prefill attention unaligned {odd} hd={hd} hq={hq} P={P} t0={t0} lr={lr}")
+    rows, G, T = 2, hq // hkv, P + t0 + lr
+    g = torch.Generator(device="cuda").manual_seed(hd + lr)
+
+    def operand(name, *shape):
+        n = int(np.prod(shape))
+        t = torch.randn(n + 8, generator=g, device="cuda").to(torch.bfloat16)
+        return t[int(name == odd):][:n].view(shape)
+    q = torch.randn((rows, lr, hq, hd), generator=g, device="cuda")
+    kp, vp = (operand(n, hkv, P, hd) if P else None for n in ("kpre", "vpre"))
+    ko, vo = (operand(n, rows, hkv, t0 + lr, hd) for n in ("kown", "vown"))
+    out = torch.empty((rows, lr, hq * hd), dtype=torch.bfloat16, device="cuda")
+    sr.prefill_attention(q, kp, vp, ko, vo, t0, out)
+    got = out.double().view(rows, lr, hkv, G, hd)
+    for r in range(rows):
+        for t in (0, 1, 31, 32, lr - 1):
+            k, v = (torch.cat(([a] if P else []) + [b[r]], 1)[:, : P + t0 + t + 1] for a, b in ((kp, ko), (vp, vo)))
+            ref = dev_attention64(torch, q[r, t].view(hkv, G, hd), k, v)
+            assert float((got[r, t] - ref).abs().max()) <= 1e-2 * float(ref.abs().max())
