@@ -1658,17 +1658,21 @@ constexpr int kTileRot = 7;
 static int stream_tile_rows(int M) { return M <= 32 ? 32 : (M <= 64 ? 64 : (M <= 112 ? 112 : 128)); }
 
 // Expected time (us) of a tile kernel over M x N x K with K split `splits`
-// ways, fitted to 1700 measurements on MI355X (129-5000 rows of the 8B, 1B and
-// small shapes' projections; rms error 11 %, the choice by it on average 1.8 %
-// slower than the best of them): a start, per round of work-groups a fixed
-// part and the K steps, and the reduction of the partials.  256-column and
-// 128-column tiles run one work-group a CU; of the 128 x 128 tiles two share a
-// CU, at 0.95 us a step together against 0.62 us alone.  Rows are counted in
-// whole 128s, so the choice is the same within each.
-// Partials that the next kernel sums itself (`fused`) cost that kernel their
-// bytes and nothing else: 512 rows of the 8B QKV projection take 33 us in two
-// splits of 256 x 128 tiles and 52 us unsplit in 128 x 128 ones, where a
-// reduction launch would add 17 us to the former.
+// ways: a start, per round of work-groups a fixed part and the K steps, and
+// what the partials of a split cost (their stores, the reduction launch and its
+// loads).  256-column and 128-column tiles run one work-group a CU; of the
+// 128 x 128 tiles two share a CU, at 0.95 us a step together against 0.67 us
+// alone.  Rows are counted in whole 128s, so the choice is the same within
+// each.  The constants minimise the time of the chosen plans over 6600
+// measurements on MI355X (129-32768 rows of the 8B, 1B and small shapes'
+// projections, weights from HBM; profiles/gemm_plan_sweep.csv): the choice is
+// on average 0.7 % slower than the best plan of a shape, at most 13 %, except
+// where the last row tile is nearly full but ragged: its element-wise epilogue
+// is not modelled, and a choice costs up to 44 %.
+// The partials: 512 rows of the 8B QKV projection take 39.8 us in two splits of
+// 256 x 128 tiles with their reduction and 50.9 us unsplit in 128 x 128 ones (a
+// reduction priced at twice its time, as by scalar loads, chose the latter).
+// Partials that the next kernel sums itself (`fused`) cost their bytes only.
 static double tile_cost(GemmKind kind, int M, int N, int K, bool paired, int splits, bool fused) {
   const int bm = kind == GEMM_TILE128 ? 128 : 256;
   const int bn = (kind == GEMM_TILE128 || kind == GEMM_DMA3 ? 128 : 256) / (paired ? 2 : 1);
@@ -1679,16 +1683,16 @@ static double tile_cost(GemmKind kind, int M, int N, int K, bool paired, int spl
   if (kind == GEMM_TILE128) {
     const double full = (double)(groups / 512);
     const int64_t rest = groups % 512;
-    t = 3.2 + (full * 0.95 + (rest == 0 ? 0.0 : (rest <= 256 ? 0.62 : 0.95))) * steps + (full + (rest > 0)) * 2.4;
+    t = 3.2 + (full * 0.95 + (rest == 0 ? 0.0 : (rest <= 256 ? 0.67 : 0.95))) * steps + (full + (rest > 0)) * 2.1;
   } else if (kind == GEMM_DMA3) {
-    t = 3.2 + one * (0.69 * steps + 4.4);
+    t = 3.2 + one * (0.77 * steps + 4.9);
   } else {
-    t = 3.2 + one * (1.07 * steps + 8.8);
+    t = 3.2 + one * (1.14 * steps + 11.1);
   }
   const double rows = (M + 127) / 128 * 128.0;
   if (splits > 1) {
-    t += fused ? 0.33e-6 * 4.0 * (splits - 1) * rows * N
-               : 5.0 + 0.33e-6 * 4.0 * (splits * (paired ? 2 : 1) + 1) * rows * N;
+    t += fused ? 0.22e-6 * 4.0 * (splits - 1) * rows * N
+               : 2.9 + 0.2e-6 * 4.0 * (splits * (paired ? 2 : 1) + 1) * rows * N;
   }
   return t;
 }
