@@ -1624,7 +1624,7 @@ static void launch_bf16(const GemmArgs& g, int splits, int kps, const EpiArgs& e
 
 size_t gemm_partial_elems(int dtype, int M, int N, int K, bool paired) {
   GemmPlan p = gemm_plan(dtype, M, N, K, paired, false);
-  if (p.splits <= 1 && dtype == SR_BF16) return 0;
+  if (p.splits <= 1) return 0;   // (fp32 never splits into partials)
   return (size_t)p.splits * M * (paired ? 2 * (size_t)N : (size_t)N);
 }
 

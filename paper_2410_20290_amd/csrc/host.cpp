@@ -164,8 +164,9 @@ static Plan make_plan(const Dims& g, const Dims& rm, int P, const sr_params* p) 
   size_t gp = 0;
   for (const Dims* m : {&g, &rm}) {
     if (m->dtype == SR_F32) {
-      size_t ncol = std::max({(size_t)m->qkv, (size_t)m->d, (size_t)2 * m->ff, (size_t)m->V});
-      gp = std::max(gp, (size_t)Mmax * ncol);
+      // fp32 projections sum their K split themselves: only the decode ones,
+      // whose consumers read partials, write any
+      if (m == &g) gp = std::max(gp, (size_t)pl.N * std::max(m->qkv, m->d));
     } else {
       auto upto = [&](int M, int N, int K, bool paired, bool fused) {
         gp = std::max(gp, gemm_partial_elems_upto(m->dtype, M, N, K, paired, fused));
@@ -1198,7 +1199,6 @@ sr_status sr_compact(const void* src, int64_t src_block_elems, void* dst, int64_
 
 size_t sr_projection_scratch(int32_t dtype, int32_t M, int32_t N, int32_t K, int32_t mode) {
   if (M < 0 || N < 0 || K < 0 || mode < 0 || mode > 3) return 0;
-  if (dtype == SR_F32) return (size_t)M * (mode == 2 ? 2 * (size_t)N : (size_t)N);
   return gemm_partial_elems(dtype, M, N, K, mode == 2);
 }
 

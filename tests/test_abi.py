@@ -96,6 +96,22 @@ def test_reward_cache_size():
     assert b[0] == b[1]
 
 
+def test_fp32_projections_need_no_partials(L):
+    """The fp32 tiles sum their K split themselves: no scratch, and a workspace
+    without partials for the chunked passes (each buffer is at most twice the
+    bf16 pair's, up to the decode partials of n rows)."""
+    for M, N, K in ((5, 96, 128), (3000, 384, 512)):
+        for mode in range(4):
+            assert L.sr_projection_scratch(sr.SR_F32, M, N, K, mode) == 0
+    c = synth.CONFIGS["tiny_fp32"]
+    m = c.model
+    p = sr.make_params(512, 0.8, 64, 512)
+    size = {dt: ws_size(L, fake_model(m, False, dt), fake_model(m, True, dt), 64, p) for dt in (sr.SR_F32, sr.SR_BF16)}
+    assert all(st == sr.SR_OK for st, _ in size.values())
+    qkv = (m.n_heads + 2 * m.n_kv_heads) * m.head_dim
+    assert size[sr.SR_F32][1] <= 2 * size[sr.SR_BF16][1] + 4 * p.n * max(qkv, m.d_model)
+
+
 def plan(L, gen, rm, P, p, cap):
     out = sr.sr_params()
     st = L.sr_plan_for_memory(ctypes.byref(gen), ctypes.byref(rm), P, ctypes.byref(p), cap, ctypes.byref(out))
