@@ -84,7 +84,7 @@ __device__ __forceinline__ uint32_t lds_addr(const bf16_t* p) {
 // (vmcnt 0), they leave the next tile's copies flying.
 template <int N, int LO, int HI>
 __device__ __forceinline__ void lds_read_tr16_pairs(const uint32_t (&a)[N], i16x4 (&lo)[N], i16x4 (&hi)[N]) {
-  static_assert(N == 2 || N == 4 || N == 8, "pairs");
+  static_assert(N == 2 || N == 4, "pairs");
   if constexpr (N == 2) {
     asm volatile(
         "ds_read_b64_tr_b16 %0, %4 offset:%6\n\tds_read_b64_tr_b16 %1, %4 offset:%7\n\t"
@@ -126,18 +126,18 @@ __global__ void __launch_bounds__(256)
 decode_attn_kernel(const float* __restrict__ q, const T* __restrict__ kpre, const T* __restrict__ vpre,
                    int P, const T* __restrict__ ktail, const T* __restrict__ vtail, int cap, int lt,
                    int hq, int hkv, int kps, int splits, float* __restrict__ part,
-                   T* __restrict__ out, float qscale, int key0, int split0) {
+                   T* __restrict__ out, float qscale) {
   constexpr int EPL = Vec16<T>::N;   // elements per 16-byte load
   constexpr int LPK = HD / EPL;      // lanes per key row
   constexpr int KPW = 64 / LPK;      // keys per wave step
   constexpr int U = 4;               // keys per lane per iteration
   constexpr int NW = 4;              // waves
-  // keys [key0, P + lt) in splits of kps; partial slot split0 + split
+  // keys [0, P + lt) in splits of kps
   const int split = blockIdx.x, h = blockIdx.y, row = blockIdx.z;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int sub = lane % LPK, ks = lane / LPK;
   const int total = P + lt;
-  const int k0 = key0 + split * kps, k1 = min(total, k0 + kps);
+  const int k0 = split * kps, k1 = min(total, k0 + kps);
 
   float qv[G][EPL];
 #pragma unroll
@@ -279,7 +279,7 @@ decode_attn_kernel(const float* __restrict__ q, const T* __restrict__ kpre, cons
     if (out) {
       out[((int64_t)row * hq + qh) * HD + dd] = from_f32<T>(A / L);
     } else {
-      float* p = part + (((int64_t)row * hq + qh) * splits + split0 + split) * (HD + 2);
+      float* p = part + (((int64_t)row * hq + qh) * splits + split) * (HD + 2);
       p[dd] = A;
       if (dd == 0) {
         p[HD] = M;
@@ -987,24 +987,20 @@ constexpr int kWaveTarget = 2048;
 // part_splits partial slots per (row, query head) in `part` (unnormalised
 // output, running max, sum); they are folded in by log-sum-exp and the
 // attention output is written.
-template <int HD, int G>
-__global__ void __launch_bounds__(64 * G)
+__global__ void __launch_bounds__(64)
 prefix_attn_mfma_kernel(const float* __restrict__ q, const bf16_t* __restrict__ kpre, const bf16_t* __restrict__ vpre,
                         int P, int rows, int hq, bf16_t* __restrict__ out, float qscale,
                         const float* __restrict__ part, int part_splits) {
-  constexpr int NT = 64 * G;
+  constexpr int HD = 128, NT = 64;
   constexpr int KT = 32;             // keys per staged tile
   constexpr int KS = HD / 32, DT = HD / 16, CPK = HD / 8;
   constexpr int PF_KROW = HD + 8;    // K tile row (bf16), padded
   constexpr int PF_VROW = HD + 16;   // V tile row (bf16), padded: the 8-byte transpose reads of a
                                      // half wave (eight rows) fall on distinct banks
-  static_assert(HD == 64 || HD == 128, "head_dim");
   __shared__ __attribute__((aligned(16))) bf16_t Ks[KT * PF_KROW];
   __shared__ __attribute__((aligned(16))) bf16_t Vs[KT * PF_VROW];
   const int h = blockIdx.y;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int fr = lane & 15, fg = lane >> 4;
-  const int qh = h * G + wave;
+  const int fr = threadIdx.x & 15, fg = threadIdx.x >> 4;
   const int t = blockIdx.x * 16 + fr;      // this lane's decode row
   const bool qvalid = t < rows;
   // Q^T fragments: lane holds Q[t][32 s + 8 fg .. +8] for k-step s (scaled,
@@ -1012,7 +1008,7 @@ prefix_attn_mfma_kernel(const float* __restrict__ q, const bf16_t* __restrict__ 
   bf16x8 qf[KS];
   {
     const float sc = qvalid ? qscale : 0.f;
-    const float4* qr = reinterpret_cast<const float4*>(q + ((int64_t)min(t, rows - 1) * hq + qh) * HD);
+    const float4* qr = reinterpret_cast<const float4*>(q + ((int64_t)min(t, rows - 1) * hq + h) * HD);
     float4 qv[2 * KS];
 #pragma unroll
     for (int st = 0; st < KS; ++st) {
@@ -1121,9 +1117,9 @@ prefix_attn_mfma_kernel(const float* __restrict__ q, const bf16_t* __restrict__ 
     lds_barrier();
   }
   if (qvalid) {
-    // fold in the tail partials of (row t, head qh): slot s holds the
+    // fold in the tail partials of (row t, head h): slot s holds the
     // unnormalised output, its maximum and its sum
-    const float* pr = part + ((int64_t)t * hq + qh) * part_splits * (HD + 2);
+    const float* pr = part + ((int64_t)t * hq + h) * part_splits * (HD + 2);
     float mx = m;
     for (int sp = 0; sp < part_splits; ++sp) mx = fmaxf(mx, pr[sp * (HD + 2) + HD]);
     const float c0 = exp2_or_zero(m - mx);
@@ -1140,7 +1136,7 @@ prefix_attn_mfma_kernel(const float* __restrict__ q, const bf16_t* __restrict__ 
         for (int i = 0; i < 4; ++i) o[dt][i] += ps[dt * 16 + 4 * fg + i] * cs;
     }
     const float inv = 1.0f / L;
-    bf16_t* orow = out + ((int64_t)t * hq + qh) * HD;
+    bf16_t* orow = out + ((int64_t)t * hq + h) * HD;
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
@@ -1148,10 +1144,11 @@ prefix_attn_mfma_kernel(const float* __restrict__ q, const bf16_t* __restrict__ 
   }
 }
 
-// Whether the shared prefix is attended by the batched MFMA kernel (from 128
-// rows; below that it costs more than the L2 reads it saves).
-static bool prefix_by_mfma(int dtype, int hd, int P, int rows) {
-  return dtype == SR_BF16 && hd == 128 && P > 0 && rows >= 128;
+// Whether the shared prefix is attended by the batched MFMA kernel: one query
+// head per KV head (more take the row groups from 64 rows), from 128 rows
+// (below that it costs more than the L2 reads it saves).
+static bool prefix_by_mfma(int dtype, int hd, int g, int P, int rows) {
+  return dtype == SR_BF16 && hd == 128 && g == 1 && P > 0 && rows >= 128;
 }
 
 // Partial slots needed for `keys` = prefix + maximal tail (upper bound for
@@ -1250,82 +1247,57 @@ static void launch_wave(const DecodeAttnArgs& a, bool prefix, const WavePlan& w,
 template <typename T, int HD, int G>
 static void launch_decode(const DecodeAttnArgs& a, hipStream_t s) {
   const float qscale = kLog2e / sqrtf((float)HD);
-  // The batched MFMA pass over the shared prefix (16 rows per work-group)
-  // runs last: the tails leave partial slots and it folds them into its own
-  // result, so no merge pass is needed.
-  auto prefix_pass = [&](int tsplits) {
-    SR_LAUNCH((prefix_attn_mfma_kernel<128, G>), dim3((a.rows + 15) / 16, a.hkv), dim3(64 * G), 0, s, a.q,
-              (const bf16_t*)a.kpre, (const bf16_t*)a.vpre, a.P, a.rows, a.hq, (bf16_t*)a.out, qscale, a.part, tsplits);
-    SR_CHECK_LAUNCH();
-  };
-  if constexpr ((HD == 64 || HD == 128) && (G == 2 || G == 4 || G == 8)) {
-    if (group_form(a.dtype, HD, G, a.P, a.rows)) {
-      SR_REQUIRE(!a.qpart || (a.lt >= 1 && a.rope && a.qsplits >= 1), SR_ERR_INTERNAL,
-                 "fused QKV finalize needs a new key");
-      launch_group<HD, G>(a, qscale, s);
-      return;
-    }
-  }
-  if constexpr (HD == 64 || HD == 128) {
-    if (wave_form(a.dtype, HD, G)) {
-      // the key-split kernel over the keys past the prefix pass's, then the
-      // prefix pass or (several splits without it) the merge
-      const bool pre = prefix_by_mfma(a.dtype, HD, a.P, a.rows);
-      SR_REQUIRE(!a.qpart || (a.lt >= 1 && a.rope && a.qsplits >= 1), SR_ERR_INTERNAL,
-                 "fused QKV finalize needs a new key");
-      const int pkeys = pre ? 0 : a.P;
-      if (pkeys + a.lt > 0) {
-        const WavePlan w = wave_plan(a.rows, a.hkv, pkeys, a.lt);
-        const bool direct = !pre && w.splits == 1;
-        if (!direct)
-          SR_REQUIRE((size_t)a.rows * a.hq * w.splits * (HD + 2) <= a.part_cap, 5,
-                     "attention partial buffer too small");
-        DecodeAttnArgs b = a;
-        if (!pre) b.qout = nullptr;  // only the prefix pass reads q back
-        launch_wave<HD, G>(b, !pre, w, direct, qscale, s);
-        if (pre) {
-          prefix_pass(w.splits);
-        } else if (!direct) {
-          SR_LAUNCH((decode_merge_kernel<T, HD>), dim3(a.rows * a.hq), dim3(HD), 0, s, a.part, w.splits,
-                             (T*)a.out);
-          SR_CHECK_LAUNCH();
-        }
-      } else {
-        prefix_pass(0);
+  int splits = 0;
+  if constexpr (std::is_same<T, bf16_t>::value && (HD == 64 || HD == 128)) {
+    SR_REQUIRE(!a.qpart || (a.lt >= 1 && a.rope && a.qsplits >= 1), SR_ERR_INTERNAL,
+               "fused QKV finalize needs a new key");
+    if constexpr (G != 1) {
+      if (group_form(a.dtype, HD, G, a.P, a.rows)) {
+        launch_group<HD, G>(a, qscale, s);
+        return;
       }
-      return;
     }
-  }
-  SR_REQUIRE(!a.qpart, SR_ERR_INTERNAL, "fused QKV finalize without the MFMA decode kernels");
-  if (prefix_by_mfma(a.dtype, HD, a.P, a.rows)) {
-    // tail partials, then the prefix pass
-    const int tkps = a.lt > 0 ? decode_kps(a.rows, a.hkv, a.lt) : 1;
-    const int tsplits = (a.lt + tkps - 1) / tkps;
-    SR_REQUIRE((size_t)a.rows * a.hq * std::max(tsplits, 1) * (HD + 2) <= a.part_cap, 5,
-               "attention partial buffer too small");
-    if (tsplits > 0) {
-      SR_LAUNCH((decode_attn_kernel<T, HD, G>), dim3(tsplits, a.hkv, a.rows), dim3(256), 0, s, a.q,
-                         (const T*)a.kpre, (const T*)a.vpre, a.P, (const T*)a.ktail, (const T*)a.vtail, a.cap,
-                         a.lt, a.hq, a.hkv, tkps, tsplits, a.part, (T*)nullptr, qscale, a.P, 0);
-      SR_CHECK_LAUNCH();
+    // the key-split kernel over the keys past the prefix pass's, then the
+    // prefix pass or (several splits without it) the merge
+    const bool pre = prefix_by_mfma(a.dtype, HD, G, a.P, a.rows);
+    const int pkeys = pre ? 0 : a.P;
+    if (pkeys + a.lt > 0) {
+      const WavePlan w = wave_plan(a.rows, a.hkv, pkeys, a.lt);
+      splits = w.splits;
+      const bool direct = !pre && splits == 1;
+      if (!direct)
+        SR_REQUIRE((size_t)a.rows * a.hq * splits * (HD + 2) <= a.part_cap, 5, "attention partial buffer too small");
+      DecodeAttnArgs b = a;
+      if (!pre) b.qout = nullptr;  // only the prefix pass reads q back
+      launch_wave<HD, G>(b, !pre, w, direct, qscale, s);
     }
-    prefix_pass(tsplits);
-    return;
+    if constexpr (HD == 128 && G == 1) {
+      // The batched pass over the shared prefix (16 rows per work-group) runs
+      // last: the tails left partial slots and it folds them into its own
+      // result, so no merge pass is needed.
+      if (pre) {
+        SR_LAUNCH(prefix_attn_mfma_kernel, dim3((a.rows + 15) / 16, a.hkv), dim3(64), 0, s, a.q, (const bf16_t*)a.kpre,
+                  (const bf16_t*)a.vpre, a.P, a.rows, a.hq, (bf16_t*)a.out, qscale, a.part, splits);
+        SR_CHECK_LAUNCH();
+        return;
+      }
+    }
+  } else {
+    SR_REQUIRE(!a.qpart, SR_ERR_INTERNAL, "fused QKV finalize without the MFMA decode kernels");
+    const int keys = a.P + a.lt;
+    const int kps = decode_kps(a.rows, a.hkv, keys);
+    splits = (keys + kps - 1) / kps;
+    if (splits > 1)
+      SR_REQUIRE((size_t)a.rows * a.hq * splits * (HD + 2) <= a.part_cap, 5,
+                 "attention partial buffer too small");
+    SR_LAUNCH((decode_attn_kernel<T, HD, G>), dim3(splits, a.hkv, a.rows), dim3(256), 0, s,
+                       a.q, (const T*)a.kpre, (const T*)a.vpre, a.P, (const T*)a.ktail,
+                       (const T*)a.vtail, a.cap, a.lt, a.hq, a.hkv, kps, splits, a.part,
+                       splits == 1 ? (T*)a.out : (T*)nullptr, qscale);
+    SR_CHECK_LAUNCH();
   }
-  const int keys = a.P + a.lt;
-  const int kps = decode_kps(a.rows, a.hkv, keys);
-  const int splits = (keys + kps - 1) / kps;
-  if (splits > 1)
-    SR_REQUIRE((size_t)a.rows * a.hq * splits * (HD + 2) <= a.part_cap, 5,
-               "attention partial buffer too small");
-  SR_LAUNCH((decode_attn_kernel<T, HD, G>), dim3(splits, a.hkv, a.rows), dim3(256), 0, s,
-                     a.q, (const T*)a.kpre, (const T*)a.vpre, a.P, (const T*)a.ktail,
-                     (const T*)a.vtail, a.cap, a.lt, a.hq, a.hkv, kps, splits, a.part,
-                     splits == 1 ? (T*)a.out : (T*)nullptr, qscale, 0, 0);
-  SR_CHECK_LAUNCH();
   if (splits > 1) {
-    SR_LAUNCH((decode_merge_kernel<T, HD>), dim3(a.rows * a.hq), dim3(HD), 0, s, a.part,
-                       splits, (T*)a.out);
+    SR_LAUNCH((decode_merge_kernel<T, HD>), dim3(a.rows * a.hq), dim3(HD), 0, s, a.part, splits, (T*)a.out);
     SR_CHECK_LAUNCH();
   }
 }
@@ -1374,15 +1346,11 @@ size_t decode_attn_part_floats(const DecodeAttnArgs& a) {
   const size_t per = (size_t)a.rows * a.hq * (a.hd + 2);
   if (group_form(a.dtype, a.hd, g, a.P, a.rows)) return 0;
   if (wave_form(a.dtype, a.hd, g)) {
-    const bool pre = prefix_by_mfma(a.dtype, a.hd, a.P, a.rows);
+    const bool pre = prefix_by_mfma(a.dtype, a.hd, g, a.P, a.rows);
     const int pkeys = pre ? 0 : a.P;
     if (pkeys + a.lt <= 0) return 0;
     const WavePlan w = wave_plan(a.rows, a.hkv, pkeys, a.lt);
     return (!pre && w.splits == 1) ? 0 : per * w.splits;
-  }
-  if (prefix_by_mfma(a.dtype, a.hd, a.P, a.rows)) {
-    const int tkps = a.lt > 0 ? decode_kps(a.rows, a.hkv, a.lt) : 1;
-    return per * std::max((a.lt + tkps - 1) / tkps, 1);
   }
   const int keys = a.P + a.lt;
   const int kps = decode_kps(a.rows, a.hkv, keys);
