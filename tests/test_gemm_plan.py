@@ -9,6 +9,7 @@ import os
 import pytest
 
 import paper_2410_20290_amd as sr
+from test_gpu_gemm import KERNEL_SHAPES
 
 KINDS = ["reg", "stream", "tile128", "tile256", "wring", "dma3"]
 
@@ -73,3 +74,43 @@ def test_streaming_plans_are_near_the_fastest_measured():
             loss.append(us[plan(M, N, K, paired, fused)] / min(us.values()))
     assert len(loss) > 150
     assert sum(loss) / len(loss) <= 1.01 and max(loss) <= 1.2
+
+
+@pytest.mark.parametrize("kernel,splits,mode,M,N,K", KERNEL_SHAPES)
+def test_kernel_shapes_reach_their_kernel(kernel, splits, mode, M, N, K):
+    assert plan(M, N, K, mode == 2) == (kernel, splits)
+
+
+def test_kernel_shapes_cover_every_tile_kernel():
+    have = {(k, mode == 2, s > 1) for k, s, mode, _, _, _ in KERNEL_SHAPES}
+    for k in ("tile128", "tile256", "dma3"):
+        assert {(k, p, s) for p in (False, True) for s in (False, True)} <= have
+    assert {("wring", False, False), ("wring", True, False)} <= have   # (never split)
+
+
+@pytest.mark.parametrize("N,K,paired", [(6144, 4096, False), (4096, 4096, False), (4096, 14336, False),
+                                        (14336, 4096, True), (128256, 4096, False), (3072, 2048, False),
+                                        (2048, 8192, False), (768, 512, False), (512, 1536, False), (384, 320, False),
+                                        (8192, 2048, True)])
+@pytest.mark.parametrize("fused", [False, True])
+def test_partials_of_every_row_count_fit_the_workspace(N, K, paired, fused):
+    """The workspace is sized by gemm_partial_elems_upto from the ends of the
+    blocks of rows: no call of up to M_max rows writes more, for limits at a
+    block's end and inside one, and it grows with M_max."""
+    if paired and fused:
+        pytest.skip("partials are left by unpaired projections only")
+    upto = sr.lib()._ZN2sr23gemm_partial_elems_uptoEiiiibb
+    upto.restype, upto.argtypes = ctypes.c_size_t, [ctypes.c_int] * 4 + [ctypes.c_bool] * 2
+
+    def partials(M):
+        s = plan(M, N, K, paired, fused)[1]
+        return s * M * N * (2 if paired else 1) if s > 1 or fused else 0
+    most, at = 0, {}
+    for M in range(1, 2601):
+        most = max(most, partials(M))
+        at[M] = most
+    last = 0
+    for M in (1, 31, 32, 33, 64, 65, 100, 112, 113, 128, 129, 200, 256, 257, 500, 512, 513, 1000, 1024, 1025, 2000, 2600):
+        n = int(upto(sr.SR_BF16, M, N, K, paired, fused))
+        assert n >= at[M] and n >= last, (M, n, at[M])
+        last = n

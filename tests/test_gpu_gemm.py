@@ -19,7 +19,7 @@ def bf16_round(a):
 SHAPES = [(1, 64, 64), (17, 100, 128), (33, 1000, 512), (100, 384, 4096), (129, 130, 64), (300, 257, 1024),
           (512, 512, 14336), (1000, 96, 192), (1100, 300, 256), (2048, 520, 1024), (4000, 129, 64),
           (128, 200, 1024), (64, 64, 14336), (21, 4100, 1792), (112, 130, 384),
-          # a few hundred rows with enough 256 x 256 tiles for the three-deep weight ring
+          # a few hundred rows, many columns, short K (128 x 128 tiles)
           (300, 49152, 256), (257, 24576, 128),
           # the 103-row QKV projection of the 8B shape
           (103, 6144, 4096),
@@ -31,13 +31,13 @@ SHAPES = [(1, 64, 64), (17, 100, 128), (33, 1000, 512), (100, 384, 4096), (129, 
           (103, 66000, 384), (70, 65601, 128),
           # paired few-row tiles with 512-byte rows per copy (K steps of 256), ragged N
           (21, 4100, 2048),
-          # thousands of rows, ragged in M and N, ten K steps (the 256 x 256 tile)
+          # thousands of rows, ragged in M and N, ten K steps
           (2600, 1100, 640),
           # 128 x 128 tiles: one to four K steps, ragged edges, one and two
           # work-groups a CU, K split; the rows where the choice changes
           (113, 130, 64), (129, 127, 128), (300, 200, 192), (771, 2048, 512), (513, 4100, 256), (200, 2048, 2048),
           (640, 300, 3072), (1500, 1000, 448),
-          # 256 x 256 tiles in five LDS slots: one to five K steps
+          # thousands of rows, one to five K steps
           (5000, 2600, 64), (5100, 2570, 128), (4900, 2600, 320),
           # few rows, short K: no split where a reduction would cost more
           (64, 1536, 512), (21, 8192, 512)]
@@ -82,6 +82,43 @@ def test_projection(dtype, mode, M, N, K):
     scale = np.abs(ref).max()
     rtol = 1e-2 if (mode in (2, 3) and dtype == "bf16") else 1e-4
     assert np.abs(got - ref).max() <= rtol * scale, np.abs(got - ref).max()
+
+
+# (kernel, splits, mode, M, N, K): every tile kernel paired and not, with and
+# without a K split, at each remainder of its three-step loop, ragged in M and N;
+# that the plans are these is asserted without a GPU (test_gemm_plan.py)
+KERNEL_SHAPES = [("dma3", 1, 1, 129, 16390, 1024), ("dma3", 1, 3, 256, 16390, 1088), ("dma3", 1, 0, 129, 16390, 1152),
+                 ("dma3", 1, 2, 129, 8200, 1024), ("dma3", 1, 2, 129, 8200, 1088), ("dma3", 1, 2, 129, 8200, 1152),
+                 ("dma3", 8, 1, 129, 2050, 8192), ("dma3", 8, 0, 200, 4096, 14336), ("dma3", 4, 2, 129, 2050, 4096),
+                 ("tile256", 1, 1, 1500, 8200, 640), ("tile256", 1, 3, 1500, 8200, 704),
+                 ("tile256", 1, 0, 3100, 2570, 1152), ("tile256", 1, 2, 1500, 4100, 640),
+                 ("tile256", 1, 2, 1500, 4100, 704), ("tile256", 1, 2, 1500, 4100, 768),
+                 ("tile256", 4, 1, 771, 4096, 14336), ("tile256", 4, 3, 129, 8200, 8192),
+                 ("tile256", 8, 2, 129, 2050, 14336),
+                 ("wring", 1, 0, 129, 40000, 1024), ("wring", 1, 3, 129, 40000, 1088), ("wring", 1, 1, 129, 40000, 1152),
+                 ("wring", 1, 2, 129, 24600, 640), ("wring", 1, 2, 129, 24600, 704), ("wring", 1, 2, 200, 16390, 1152),
+                 ("tile128", 2, 1, 129, 257, 1152), ("tile128", 2, 3, 129, 257, 1024), ("tile128", 8, 0, 129, 257, 8192),
+                 ("tile128", 2, 2, 129, 257, 1152), ("tile128", 1, 0, 300, 514, 256), ("tile128", 1, 2, 300, 514, 192)]
+
+
+@pytest.mark.parametrize("kernel,splits,mode,M,N,K", KERNEL_SHAPES)
+def test_projection_tile_kernels(kernel, splits, mode, M, N, K):
+    torch, sr = need_gpu()
+    say(f"projection {kernel} splits={splits} mode={mode} M={M} N={N} K={K}")
+    bf = torch.bfloat16
+    g = torch.Generator(device="cuda").manual_seed(M + N + K + mode)
+    x = torch.empty((M, K), dtype=bf, device="cuda").normal_(0, 1, generator=g)
+    w = torch.empty((2, N, K) if mode == 2 else (N, K), dtype=bf, device="cuda").normal_(0, 0.05, generator=g)
+    out = torch.randn((M, N), generator=g, device="cuda").to(bf if mode >= 2 else torch.float32)
+    x64, w64 = x.double(), w.double()
+    if mode == 2:
+        ga, up = x64 @ w64[0].T, x64 @ w64[1].T
+        ref = ga / (1 + torch.exp(-ga)) * up
+    else:
+        ref = x64 @ w64.T + (out.double() if mode == 1 else 0)
+    sr.projection(x, w, mode, out)
+    torch.cuda.synchronize()
+    assert float((out.double() - ref).abs().max()) <= (1e-2 if mode >= 2 else 1e-4) * float(ref.abs().max())
 
 
 @pytest.mark.parametrize("M", [8, 41, 103, 120])
