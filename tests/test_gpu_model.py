@@ -109,6 +109,44 @@ def test_teacher_forced_many_rows_head_dim_128():
         assert np.abs(lg[r] - refl).max() <= 2e-2 * np.abs(refl).max(), r
 
 
+@pytest.mark.parametrize("dtype,rows", [("f32", 5), ("bf16", 3), ("bf16", 70), ("bf16", 120)])
+@pytest.mark.parametrize("vocab,off", [(1001, 0), (1002, 1), (1000, 1)])
+def test_teacher_forced_odd_vocabulary(dtype, rows, vocab, off):
+    """The LM head writes straight into the caller's rows, which lie `len *
+    vocab` floats apart: vocabularies that are no multiple of 4, and an output
+    that starts on a 4-byte boundary.  Nothing outside the output is written."""
+    import ctypes
+    import synth
+    from oracle.transformer import Transformer
+    torch, sr = need_gpu()
+    say(f"teacher-forced {dtype} vocab={vocab} rows={rows} off={off}")
+    shape = synth.ModelShape(2, 256, 4, 2, 64, 512, vocab, dtype, 500000.0)
+    gw, rw = synth.model_weights(shape, 4, False), synth.model_weights(shape, 5, True)
+    gen, rm = sr.DeviceModel.upload(shape, gw, False), sr.DeviceModel.upload(shape, rw, True)
+    prompt = synth.tokens(21, vocab, 6)
+    length = 5
+    toks = np.random.default_rng(8).integers(0, vocab, size=(rows, length)).astype(np.int32)
+    p = sr.make_params(rows, 0.5, length, length)
+    ws = sr.Workspace(gen, rm, len(prompt), p)
+    n = rows * length * vocab
+    buf = torch.full((n + off + 8,), 7.0, device="cuda")
+    td = torch.from_numpy(toks).cuda()
+    pr = np.ascontiguousarray(prompt, dtype=np.int32)
+    st = sr.lib().sr_logits_teacher_forced(ctypes.byref(gen.desc), ctypes.byref(rm.desc), pr.ctypes.data, len(pr),
+                                           ctypes.byref(p), td.data_ptr(), rows, length, buf.data_ptr() + 4 * off,
+                                           ws.ptr, ws.nbytes, None)
+    assert st == sr.SR_OK, sr.last_error()
+    torch.cuda.synchronize()
+    got = buf.cpu().numpy()
+    assert (got[:off] == 7.0).all() and (got[off + n:] == 7.0).all()
+    lg = got[off:off + n].reshape(rows, length, vocab)
+    og = Transformer(shape, gw, False)
+    rtol = 1e-4 if dtype == "f32" else 2e-2
+    for r in sorted({0, rows // 2, rows - 1}):
+        ref = og.logits(list(prompt) + list(toks[r]))[len(prompt) - 1: len(prompt) - 1 + length]
+        assert np.abs(lg[r] - ref).max() <= rtol * np.abs(ref).max(), r
+
+
 def test_8b_layer_shapes_at_run_row_counts():
     """The 8B shape's layers (d 4096, 32 query / 8 KV heads of 128, ffn
     14336, vocab 128256, RoPE theta 5e5, prompt 256) with two of them, so the
