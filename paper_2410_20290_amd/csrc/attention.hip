@@ -16,9 +16,9 @@
 //                        one-query-head-per-KV-head case at 128+ rows.
 // Online softmax in base 2; split partials are merged by log-sum-exp.
 //
-// Prefill (reward-model scoring, prompt): a work-group owns 8 / G blocks of
-// 32 queries of one row and one KV head (MFMA flash attention, bf16
-// head_dim 64/128), or a block of queries on the vector ALU with K/V staged
+// Prefill (reward-model scoring, prompt): a work-group owns 4 / G blocks (one
+// with 8 query heads per KV head) of 32 queries of one row and one KV head
+// (MFMA flash attention, bf16 head_dim 64/128), or a block of queries on the vector ALU with K/V staged
 // in LDS as fp32.
 #include <algorithm>
 #include <cfloat>
@@ -357,12 +357,12 @@ __device__ __forceinline__ void copy_v_block(BufRsrc v, int k0, int k1, bf16_t* 
 // tail for bf16, head_dim 64 or 128, on MFMA, with the keys split between the
 // NW waves of a work-group (and between `splits` work-groups per (row, KV
 // head)): each wave streams its own contiguous run of bpw 32-key blocks and
-// waits on no other wave until the final merge.  Work-group = (split, KV head, row); the G query
-// heads of the KV head are the MFMA's 16 columns (columns >= G are zero
-// queries whose results are dropped).
+// waits on no other wave until the final merge.  Work-group = (split, KV head,
+// row); the G query heads of the KV head are the MFMA's 16 columns (columns
+// >= G are zero queries whose results are dropped).
 //   S^T = K Q^T: the A operand (16 keys x 32 dims) is loaded from memory
 //         straight into registers, 16 bytes of one key row per lane.
-//   O^T += V^T P^T: a V block is copied memory -> LDS (global_load_lds into
+//   O^T += V^T P^T: a V block is copied memory -> LDS (buffer loads into
 //         the wave's own double buffer) and the A operand (16 dims x 32
 //         keys) comes from two LDS transpose reads; the key order of the
 //         contraction is permuted so that the B operand is the lane's own 8
@@ -374,7 +374,7 @@ __device__ __forceinline__ void copy_v_block(BufRsrc v, int k0, int k1, bf16_t* 
 // Fused QKV finalize (the decode step's QKV projection leaves split-K
 // partials): q is summed from them and rotated here, and the wave that holds
 // the newest key sums, rotates and writes its K and V row before it loads
-// any key.
+// that key's block.
 template <int HD, int G, int NW>
 __global__ void __launch_bounds__(64 * NW)
 decode_wave_kernel(const float* __restrict__ q, const bf16_t* __restrict__ kpre, const bf16_t* __restrict__ vpre,

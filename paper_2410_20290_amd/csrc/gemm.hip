@@ -3,9 +3,9 @@
 // [N][ldb] (both K-contiguous), fp32 accumulation, fused epilogues.
 //
 // bf16: MFMA tiles staged through LDS (by LDS DMA for the main kernels):
-// 256 x 256 and 256 x 128 tiles of v_mfma_f32_32x32x16_bf16 for hundreds of
-// rows and more, streaming tiles of v_mfma_f32_16x16x32_bf16 for up to 128
-// rows.  fp32: v_mfma_f32_16x16x4_f32 with operands loaded straight into
+// 256 x 256, 256 x 128 and 128 x 128 tiles of v_mfma_f32_32x32x16_bf16 for
+// more than 128 rows, streaming tiles of v_mfma_f32_16x16x32_bf16 for up to 128
+// (K a multiple of 128; the LM head up to 112).  fp32: v_mfma_f32_16x16x4_f32 with operands loaded straight into
 // their lanes (used by the fp32 model).
 // Split-K writes fp32 partials [split][M][Nout] that a consumer sums in
 // split order, so results do not depend on scheduling.
@@ -711,9 +711,9 @@ gemm_slots_kernel(const bf16_t* __restrict__ A, int lda, const bf16_t* __restric
 template <bool PAIRED>
 __global__ void __launch_bounds__(256)
 gemm_ring3_kernel(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ B, int ldb,
-                int64_t pair_off, int M, int N, int K, int k_per_split, EpiArgs epi,
-                float* __restrict__ partial) {
-  constexpr int BM = 256, BNL = 256, BK = 64;
+                  int64_t pair_off, int M, int N, int K, int k_per_split, EpiArgs epi,
+                  float* __restrict__ partial) {
+  constexpr int BM = 256, BK = 64;
   constexpr int BN_OUT = PAIRED ? 128 : 256;
   constexpr int HALF = BM * BK;           // bf16 elements of the A (or B) rows of a K step
   __shared__ __attribute__((aligned(1024))) bf16_t lds[5 * HALF];
@@ -811,9 +811,9 @@ gemm_ring3_kernel(const bf16_t* __restrict__ A, int lda, const bf16_t* __restric
     __builtin_amdgcn_sched_barrier(0);
   };
 
-  // Every step issues the DMAs of the step after next; past the last step
-  // the source is clamped to the last step (data never read), which keeps
-  // every wait below the same at each step.
+  // Every step issues the A rows two steps ahead and the B rows three; past
+  // the last step the source is clamped to the last step (data never read),
+  // which keeps every wait below the same at each step.
   issue_half(0, 0, 0);
   issue_half(0, 0, 1);
   issue_half(min(1, nk - 1), 1, 0);
@@ -827,9 +827,9 @@ gemm_ring3_kernel(const bf16_t* __restrict__ A, int lda, const bf16_t* __restric
   // registers and the next step's quarter 0 goes to (ya, yb).  bb, bbn: B
   // ring slots of steps t and t + 1.  One barrier per step, after quarter 1:
   // every wave has read the buffers of step t, and step t + 1 has landed
-  // (all but this wave's newest DMAs: none with two stages, the B rows of
-  // step t + 2 with three).  Then the A rows of step t + 2 go out under
-  // quarter 2 and the B rows of step t + 3 under quarter 3.
+  // (all but this wave's newest DMAs, the B rows of step t + 2).  Then the A
+  // rows of step t + 2 go out under quarter 2 and the B rows of step t + 3
+  // under quarter 3.
   auto step = [&](int t, int bb, int bbn, bf16x8(&xa)[4], bf16x8(&xb)[4], bf16x8(&ya)[4], bf16x8(&yb)[4],
                   bf16x8(&za)[4], bf16x8(&zb)[4]) {
     const int buf = t & 1;
@@ -890,7 +890,9 @@ gemm_ring3_kernel(const bf16_t* __restrict__ A, int lda, const bf16_t* __restric
 }
 
 
-// ------------------------- bf16 MFMA GEMM, a few hundred rows (LDS DMA)
+// -------------------- bf16 MFMA GEMM, 256 x 128 tiles, three LDS stages
+// Where a grid of 256 x 256 tiles would leave CUs idle and the K steps are
+// long enough against 128 x 128 ones (129-1024 rows of most shapes).
 // 256 x 128 block tile (PAIRED: gate and up rows interleaved in groups of
 // 32, 64 output columns), K step 64, three LDS stages of 48 KB.  With a
 // third stage the buffer refilled during step t (that of step t - 1) is
@@ -1646,8 +1648,10 @@ size_t gemm_partial_elems_upto(int dtype, int M_max, int N, int K, bool paired, 
 
 // Dispatch thresholds (rows M of the projection), measured on MI355X:
 //  - up to kStreamMaxRows rows the LDS-DMA streaming kernel (weights read
-//    once, one work-group per CU);
-//  - above, the tile kernel and K split that tile_plan expects to be fastest;
+//    once, one work-group per CU), for K a multiple of 128 and, past 64 rows,
+//    up to 65536 columns (the LM head: up to 112 rows);
+//  - else, from 65 rows, the tile kernel and K split that tile_plan expects to
+//    be fastest;
 //  - the register-staged tiles where the operands do not suit LDS DMA
 //    (dma_fits).
 constexpr int kStreamMaxRows = 128;
@@ -1663,12 +1667,12 @@ static int stream_tile_rows(int M) { return M <= 32 ? 32 : (M <= 64 ? 64 : (M <=
 // loads).  256-column and 128-column tiles run one work-group a CU; of the
 // 128 x 128 tiles two share a CU, at 0.95 us a step together against 0.67 us
 // alone.  Rows are counted in whole 128s, so the choice is the same within
-// each.  The constants minimise the time of the chosen plans over 6600
+// each.  The constants minimise the time of the chosen plans over 5300
 // measurements on MI355X (129-32768 rows of the 8B, 1B and small shapes'
 // projections, weights from HBM; profiles/gemm_plan_sweep.csv): the choice is
-// on average 0.7 % slower than the best plan of a shape, at most 13 %, except
-// where the last row tile is nearly full but ragged: its element-wise epilogue
-// is not modelled, and a choice costs up to 44 %.
+// on average 0.8 % slower than the best plan of a shape and at most 9 % where
+// the rows fill whole tiles.  The element-wise epilogue of a ragged last row
+// tile is not modelled: there a choice costs up to 26 %, in one case 44 %.
 // The partials: 512 rows of the 8B QKV projection take 39.8 us in two splits of
 // 256 x 128 tiles with their reduction and 50.9 us unsplit in 128 x 128 ones (a
 // reduction priced at twice its time, as by scalar loads, chose the latter).
@@ -1715,8 +1719,10 @@ static GemmPlan tile_plan(int M, int N, int K, bool paired, bool fused) {
         t_best = t;
       }
     }
-  // a few hundred rows on 256 x 256 tiles: the three-deep weight ring, 2 %
-  // faster there (512 rows of the 8B gate|up projection: 104.9 against 107.1 us)
+  // a few hundred rows on 256 x 256 tiles: the three-deep weight ring, 1 %
+  // faster there (8B gate|up, 129 rows: 83.2 against 89.6 us, 512 rows: 110.3
+  // against 111.6; LM head, 512 rows: 470 against 479, but 256 rows: 291
+  // against 274)
   if (best.kind == GEMM_TILE256 && best.splits == 1 && M <= kWringMaxRows) best.kind = GEMM_WRING;
   return best;
 }

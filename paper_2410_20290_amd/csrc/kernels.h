@@ -28,12 +28,12 @@ struct GemmArgs {
   int out_bf16;          // EPI_STORE / paired: 1 = bf16 out, 0 = fp32 out
 };
 enum GemmKind {
-  GEMM_REG,      // register-staged tiles (K not a multiple of what the others need, operands past 2 GiB)
+  GEMM_REG,      // register-staged tiles (up to 64 rows with K not a multiple of 128)
   GEMM_STREAM,   // LDS-DMA streaming kernels for few rows (stream, stream_bn)
   GEMM_TILE128,  // 128 x 128 tiles in five LDS slots, two work-groups a CU
   GEMM_TILE256,  // 256 x 256 tiles in five LDS slots
-  GEMM_WRING,    // 256 x 256 tiles, three-deep weight ring (a few hundred rows)
-  GEMM_DMA3      // 256 x 128 tiles, three LDS stages (a few hundred rows)
+  GEMM_WRING,    // 256 x 256 tiles, three-deep weight ring (up to 512 rows)
+  GEMM_DMA3      // 256 x 128 tiles, three LDS stages
 };
 struct GemmPlan {
   GemmKind kind;

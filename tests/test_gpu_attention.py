@@ -103,16 +103,16 @@ PREFILL_CASES = [
     # dtype, hd, hq, hkv, rows, P, t0, lr, cap
     ("bf16", 128, 32, 8, 3, 40, 37, 29, 70),      # matrix-core kernel, ragged tiles
     ("bf16", 128, 32, 8, 2, 256, 128, 100, 636),  # 8B shapes: second scoring round
-    ("bf16", 128, 32, 8, 2, 256, 0, 128, 128),    # 8B shapes: first scoring round (two 16-query blocks a work-group)
-    ("bf16", 128, 32, 8, 2, 7, 45, 130, 200),     # ragged last block, last work-group with one block
+    ("bf16", 128, 32, 8, 2, 256, 0, 128, 128),    # 8B shapes: first scoring round (one 32-query block a work-group)
+    ("bf16", 128, 32, 8, 2, 7, 45, 130, 200),     # ragged last block
     ("bf16", 64, 32, 8, 2, 30, 3, 150, 160),      # head_dim 64
-    ("bf16", 128, 16, 8, 2, 20, 5, 70, 80),       # 2 query heads per KV head: 4 blocks a work-group, 5 blocks
+    ("bf16", 128, 16, 8, 2, 20, 5, 70, 80),       # 2 query heads per KV head: 2 blocks a work-group, 3 blocks
     ("bf16", 128, 8, 8, 2, 0, 16, 33, 49),
     ("bf16", 128, 16, 2, 2, 17, 0, 50, 64),
     ("bf16", 128, 32, 8, 1, 5, 0, 1, 1),
     ("bf16", 64, 8, 2, 3, 33, 20, 17, 40),
-    # edges of the 32-query blocks, of the 64-key tiles and of the eight-wave
-    # work-groups (256 or more of them), for every group size
+    # edges of the 32-query blocks and of the 32- and 64-key tiles, grids of one
+    # work-group and of hundreds, for every group size
     ("bf16", 128, 32, 8, 1, 31, 0, 32, 32),
     ("bf16", 128, 32, 8, 1, 0, 63, 33, 96),
     ("bf16", 64, 16, 8, 1, 64, 0, 65, 65),
