@@ -159,27 +159,57 @@ void cut(const CutArgs& a, hipStream_t s) {
   SR_CHECK_LAUNCH();
 }
 
-// KV compaction.  A fixed grid walks the 16 KB chunks of the kept rows'
-// (block, row, head) runs, so a row that is not kept costs no work-group and
-// the number of kept rows stays on the device; a chunk's four loads per
-// thread go out before its stores.  With keep_flag every work-group packs
-// the flags into its own LDS list (and the first one writes src_row and
-// new_count), instead of a launch of its own before the copy.  Copy bound:
-// with 103 of 512 rows kept, 4 layers of 8 x 128 bf16 and 127 tokens (429 MB
-// moved), selection and compaction together went from 146 to 100 us.
+// keep_flag -> packed source rows and count (single work-group).
+__global__ void __launch_bounds__(kCutThreads)
+pack_flags_kernel(const int32_t* __restrict__ flag, int b, int32_t* __restrict__ src_row,
+                  int32_t* __restrict__ count) {
+  __shared__ int wsum[kCutThreads / 64];
+  int f[kCutPer], n = 0;
+#pragma unroll
+  for (int k = 0; k < kCutPer; ++k) {
+    const int i = threadIdx.x * kCutPer + k;
+    f[k] = (i < b && flag[i] != 0) ? 1 : 0;
+    n += f[k];
+  }
+  int tot;
+  int p = block_excl_scan(n, wsum, &tot);
+#pragma unroll
+  for (int k = 0; k < kCutPer; ++k) {
+    const int i = threadIdx.x * kCutPer + k;
+    if (f[k]) src_row[p++] = i;
+  }
+  if (threadIdx.x == 0) *count = tot;
+}
+
+// KV compaction: the grid walks the 16 KB chunks of the kept rows' (block, row,
+// head) runs, so a row that is not kept costs no work-group and the number of
+// kept rows stays on the device; a chunk's four loads per thread go out before
+// its stores.
+// From a row list (the generation loop) every chunk gets a work-group of its
+// own, up to kListGrid: copy bound, and a work-group that walks many chunks
+// waits for its stores between them (103 of 512 rows, 32 layers of 8 x 128 bf16,
+// 127 tokens, 3.4 GB moved: 677 us, with 2048 work-groups 724).
+// From flags (FLAGS): below kPackBytes of rows that may move, 2048 work-groups
+// pack the flags into LDS lists of their own (and the first one writes src_row
+// and new_count), which saves a launch (68 MB moved: 13.7 against 14.8 us); from
+// there one work-group packs them first and the list form follows (the 3.4 GB
+// above: 679 against 724 us; 429 MB: 82 against 88).
 constexpr int kCompactThreads = 256;
 constexpr int kCompactUnroll = 4;
-constexpr int kCompactGrid = 2048;   // eight work-groups per CU
+constexpr int kFlagGrid = 2048;      // eight work-groups per CU
+constexpr int kListGrid = 65536;
+constexpr int64_t kPackBytes = 512LL << 20;
 
+template <bool FLAGS>
 __global__ void __launch_bounds__(kCompactThreads)
 compact_kernel(const uint8_t* __restrict__ src, int64_t src_block, uint8_t* __restrict__ dst,
                int64_t dst_block, const int32_t* __restrict__ keep_flag, int b, const int32_t* __restrict__ src_row,
                const int32_t* __restrict__ count, int32_t* __restrict__ src_row_out, int32_t* __restrict__ count_out,
                int hkv, int row_bytes, int cap_src, int cap_dst, int len) {
-  __shared__ uint16_t list[kCutMax];
+  __shared__ uint16_t list[FLAGS ? kCutMax : 1];
   __shared__ int wsum[kCompactThreads / 64];
   int kept;
-  if (keep_flag) {
+  if constexpr (FLAGS) {
     // thread t packs flags [t per, (t + 1) per)
     const bool first = blockIdx.x == 0 && blockIdx.y == 0;
     const int per = (b + kCompactThreads - 1) / kCompactThreads;
@@ -207,7 +237,7 @@ compact_kernel(const uint8_t* __restrict__ src, int64_t src_block, uint8_t* __re
     const uint32_t run = w / (uint32_t)nch;
     const int c = (int)(w - run * nch);
     const int j = (int)(run / (uint32_t)hkv), h = (int)(run - j * hkv);
-    const int i = keep_flag ? list[j] : src_row[j];
+    const int i = FLAGS ? list[j] : src_row[j];
     const uint4* s4 = reinterpret_cast<const uint4*>(src + blk * src_block + (((int64_t)i * hkv + h) * cap_src) * row_bytes);
     uint4* d4 = reinterpret_cast<uint4*>(dst + blk * dst_block + (((int64_t)j * hkv + h) * cap_dst) * row_bytes);
     const int k0 = c * CH + threadIdx.x;
@@ -226,16 +256,27 @@ void compact(const CompactArgs& a, hipStream_t s) {
   const bool moves = a.max_rows > 0 && a.len > 0;
   if (!moves && !a.keep_flag) return;
   if (moves) SR_REQUIRE(row_bytes % 16 == 0, 3, "KV row must be a multiple of 16 bytes");
-  // without tokens to move, one work-group still packs the flags
   const int64_t units = (int64_t)a.len * row_bytes / 16;
   const int64_t nch = (units + kCompactThreads * kCompactUnroll - 1) / (kCompactThreads * kCompactUnroll);
   const int64_t chunks = std::max<int64_t>(1, (int64_t)a.max_rows * a.hkv * nch);
   SR_REQUIRE(units <= INT32_MAX / 2 && chunks <= INT32_MAX, SR_ERR_UNSUPPORTED, "KV pool too large to compact");
   const int blocks = moves ? 2 * a.n_layers : 1;
-  const dim3 grid((unsigned)std::min<int64_t>(chunks, std::max(1, kCompactGrid / blocks)), blocks);
-  SR_LAUNCH(compact_kernel, grid, dim3(kCompactThreads), 0, s, (const uint8_t*)a.src, a.src_block * a.elem_bytes,
-            (uint8_t*)a.dst, a.dst_block * a.elem_bytes, a.keep_flag, a.b, a.src_row, a.count, a.scratch_src_row,
-            a.new_count, a.hkv, row_bytes, a.cap_src, a.cap_dst, moves ? a.len : 0);
+  const bool pack = a.keep_flag && moves && (int64_t)a.max_rows * a.hkv * a.len * row_bytes * blocks >= kPackBytes;
+  if (pack) {
+    SR_LAUNCH(pack_flags_kernel, dim3(1), dim3(kCutThreads), 0, s, a.keep_flag, a.b, a.scratch_src_row, a.new_count);
+    SR_CHECK_LAUNCH();
+  }
+  const bool flags = a.keep_flag && !pack;   // (without tokens to move, one work-group still packs them)
+  const int32_t* src_row = pack ? a.scratch_src_row : a.src_row;
+  const int32_t* count = pack ? a.new_count : a.count;
+  const dim3 grid((unsigned)std::min<int64_t>(chunks, std::max(1, (flags ? kFlagGrid : kListGrid) / blocks)), blocks);
+#define SR_COMPACT(FLAGS)                                                                                             \
+  SR_LAUNCH(compact_kernel<FLAGS>, grid, dim3(kCompactThreads), 0, s, (const uint8_t*)a.src,                          \
+            a.src_block * a.elem_bytes, (uint8_t*)a.dst, a.dst_block * a.elem_bytes, a.keep_flag, a.b, src_row, count, \
+            a.scratch_src_row, a.new_count, a.hkv, row_bytes, a.cap_src, a.cap_dst, moves ? a.len : 0)
+  if (flags) SR_COMPACT(true);
+  else SR_COMPACT(false);
+#undef SR_COMPACT
   SR_CHECK_LAUNCH();
 }
 

@@ -139,6 +139,32 @@ def test_compact_edges(b, keep_frac, length, hkv, hd):
     assert torch.equal(dst, ref)
 
 
+@pytest.mark.parametrize("b,keep_frac,length,cap,hkv,hd,nl", [(600, 0.2, 127, 130, 4, 128, 4),   # runs of two chunks
+                                                             (600, 0.9, 16, 16, 4, 128, 32),    # more chunks than work-groups
+                                                             (600, 0.0, 127, 127, 4, 128, 4),
+                                                             (4096, 1.0, 33, 34, 2, 128, 4)])
+def test_compact_large(b, keep_frac, length, cap, hkv, hd, nl):
+    """From 512 MB of rows that may move, the flags are packed by a launch of
+    their own and the copy walks the row list."""
+    torch, sr = need_gpu()
+    say(f"compact large b={b} keep={keep_frac} len={length} hkv={hkv} hd={hd} nl={nl}")
+    assert b * hkv * length * hd * 2 * 2 * nl >= 512 << 20
+    g = torch.Generator(device="cuda").manual_seed(b + length)
+    blk = b * hkv * cap * hd
+    src = torch.randint(-2**15, 2**15, (2 * nl, b, hkv, cap, hd), generator=g, dtype=torch.int16, device="cuda")
+    flags = (torch.rand(b, generator=g, device="cuda") < keep_frac).int()
+    dst = torch.full_like(src, 3)
+    src_row = torch.full((b,), -1, dtype=torch.int32, device="cuda")
+    cnt = torch.full((1,), -1, dtype=torch.int32, device="cuda")
+    sr.compact(src, blk, dst, blk, flags, nl, hkv, hd, 2, cap, cap, length, src_row, cnt)
+    torch.cuda.synchronize()
+    kept = torch.nonzero(flags).flatten()
+    n = len(kept)
+    assert int(cnt.item()) == n and torch.equal(src_row[:n].long(), kept) and bool((src_row[n:] == -1).all())
+    assert torch.equal(dst[:, :n, :, :length], src[:, kept, :, :length])
+    assert bool((dst[:, n:] == 3).all()) and bool((dst[:, :, :, length:] == 3).all())
+
+
 @pytest.mark.parametrize("vocab", [24576, 24577, 24579, 32768, 50257, 131071, 262144])
 @pytest.mark.parametrize("temperature", [1.0, 0.3, 0.0])
 def test_sampler_segment_edges(vocab, temperature):
