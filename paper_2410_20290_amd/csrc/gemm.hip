@@ -1667,7 +1667,7 @@ static int stream_tile_rows(int M) { return M <= 32 ? 32 : (M <= 64 ? 64 : (M <=
 // loads).  256-column and 128-column tiles run one work-group a CU; of the
 // 128 x 128 tiles two share a CU, at 0.95 us a step together against 0.67 us
 // alone.  Rows are counted in whole 128s, so the choice is the same within
-// each.  The constants minimise the time of the chosen plans over 5300
+// each.  The constants minimise the time of the chosen plans over 5600
 // measurements on MI355X (129-32768 rows of the 8B, 1B and small shapes'
 // projections, weights from HBM; profiles/gemm_plan_sweep.csv): the choice is
 // on average 0.8 % slower than the best plan of a shape and at most 9 % where
