@@ -1665,17 +1665,19 @@ static int stream_tile_rows(int M) { return M <= 32 ? 32 : (M <= 64 ? 64 : (M <=
 // ways: a start, per round of work-groups a fixed part and the K steps, and
 // what the partials of a split cost (their stores, the reduction launch and its
 // loads).  256-column and 128-column tiles run one work-group a CU; of the
-// 128 x 128 tiles two share a CU, at 0.95 us a step together against 0.67 us
+// 128 x 128 tiles two share a CU, at 1.01 us a step together against 0.69 us
 // alone.  Rows are counted in whole 128s, so the choice is the same within
 // each.  The constants minimise the time of the chosen plans over 5600
 // measurements on MI355X (129-32768 rows of the 8B, 1B and small shapes'
-// projections, weights from HBM; profiles/gemm_plan_sweep.csv): the choice is
-// on average 0.8 % slower than the best plan of a shape and at most 9 % where
-// the rows fill whole tiles.  The element-wise epilogue of a ragged last row
-// tile is not modelled: there a choice costs up to 26 %, in one case 44 %.
+// projections, weights from HBM; profiles/gemm_plan_sweep.csv) with the rows
+// that fill whole tiles counted fully, as the element-wise epilogue of a ragged
+// last row tile is not modelled: the choice is on average 1.1 % slower than the
+// best plan of a shape, at most 12 % on whole tiles, up to 32 % (once 44 %) on
+// ragged ones.
 // The partials: 512 rows of the 8B QKV projection take 39.8 us in two splits of
-// 256 x 128 tiles with their reduction and 50.9 us unsplit in 128 x 128 ones (a
-// reduction priced at twice its time, as by scalar loads, chose the latter).
+// 256 x 128 tiles with their reduction and 50.9 us unsplit in 128 x 128 ones
+// (priced at 0.33 us a MB, twice what the float4 reduction takes, the latter was
+// chosen).
 // Partials that the next kernel sums itself (`fused`) cost their bytes only.
 static double tile_cost(GemmKind kind, int M, int N, int K, bool paired, int splits, bool fused) {
   const int bm = kind == GEMM_TILE128 ? 128 : 256;
@@ -1687,16 +1689,16 @@ static double tile_cost(GemmKind kind, int M, int N, int K, bool paired, int spl
   if (kind == GEMM_TILE128) {
     const double full = (double)(groups / 512);
     const int64_t rest = groups % 512;
-    t = 3.2 + (full * 0.95 + (rest == 0 ? 0.0 : (rest <= 256 ? 0.67 : 0.95))) * steps + (full + (rest > 0)) * 2.1;
+    t = 3.2 + (full * 1.01 + (rest == 0 ? 0.0 : (rest <= 256 ? 0.69 : 1.01))) * steps + (full + (rest > 0)) * 1.9;
   } else if (kind == GEMM_DMA3) {
-    t = 3.2 + one * (0.77 * steps + 4.9);
+    t = 3.2 + one * (0.77 * steps + 5.3);
   } else {
-    t = 3.2 + one * (1.14 * steps + 11.1);
+    t = 3.2 + one * (1.15 * steps + 12.0);
   }
   const double rows = (M + 127) / 128 * 128.0;
   if (splits > 1) {
-    t += fused ? 0.22e-6 * 4.0 * (splits - 1) * rows * N
-               : 2.9 + 0.2e-6 * 4.0 * (splits * (paired ? 2 : 1) + 1) * rows * N;
+    t += fused ? 0.21e-6 * 4.0 * (splits - 1) * rows * N
+               : 6.9 + 0.18e-6 * 4.0 * (splits * (paired ? 2 : 1) + 1) * rows * N;
   }
   return t;
 }

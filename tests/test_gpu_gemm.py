@@ -97,8 +97,8 @@ KERNEL_SHAPES = [("dma3", 1, 1, 129, 16390, 1024), ("dma3", 1, 3, 256, 16390, 10
                  ("tile256", 8, 2, 129, 2050, 14336),
                  ("wring", 1, 0, 129, 40000, 1024), ("wring", 1, 3, 129, 40000, 1088), ("wring", 1, 1, 129, 40000, 1152),
                  ("wring", 1, 2, 129, 24600, 640), ("wring", 1, 2, 129, 24600, 704), ("wring", 1, 2, 200, 16390, 1152),
-                 ("tile128", 2, 1, 129, 257, 1152), ("tile128", 2, 3, 129, 257, 1024), ("tile128", 8, 0, 129, 257, 8192),
-                 ("tile128", 2, 2, 129, 257, 1152), ("tile128", 1, 0, 300, 514, 256), ("tile128", 1, 2, 300, 514, 192)]
+                 ("tile128", 2, 1, 129, 257, 1536), ("tile128", 4, 3, 129, 257, 2048), ("tile128", 8, 0, 129, 257, 8192),
+                 ("tile128", 2, 2, 129, 257, 1536), ("tile128", 1, 0, 300, 514, 256), ("tile128", 1, 2, 300, 514, 192)]
 
 
 @pytest.mark.parametrize("kernel,splits,mode,M,N,K", KERNEL_SHAPES)
